@@ -35,6 +35,7 @@ size_t carve_workspace(int H, int E, int I, int kmax, int Tmax, int wfmt, void *
     w.h = (float *)take(sizeof(float) * P * I);
     w.o = (float *)take(sizeof(float) * P * H);
     w.sync = (int32_t *)take(sizeof(int32_t) * ((size_t)Tmax + 2) * kCounterStride);
+    w.tickets = w.sync + ((size_t)Tmax + 1) * kCounterStride + kTicketOff;
     if (wfmt == MOE_WFMT_NVFP4_E2M1_B16) {
         w.hb = (__bf16 *)take(2 * P * I);
         w.x16 = (_Float16 *)take((size_t)2 * Tmax * H);
@@ -345,6 +346,7 @@ static RouteParams route_params(moe_decode_t h, const void *x, int T, int k, con
     P.mstar = h->mstar;
     P.screen = T >= h->screen_min ? 1 : 0;
     P.do_group = group ? 1 : 0;
+    P.chunk = chunk_tokens(h->L, T, k);
     P.max_chunks = max_mfma_chunks(h->L.E, h->cfg.max_tokens, h->cfg.max_topk);
     return P;
 }
@@ -420,7 +422,8 @@ moe_status moe_decode_forward(moe_decode_t h, void *stream, const void *x, int32
 // carved as for a handle.  The counters are zero when the code object is loaded
 // (static storage), are cleared once more when a device is set up, and every forward
 // call leaves them at zero again (each counter is reset by the workgroup that
-// consumes it), so nothing has to be cleared per call.
+// consumes it; the large-batch kernels' item counters, in words no other counter uses, are
+// zeroed by the step's grouping), so nothing has to be cleared per call.
 constexpr size_t kScratchBytes = (size_t)64 << 20;
 constexpr size_t kScratchCounterBytes =
     ((size_t)(1024 + 2) * kCounterStride * sizeof(int32_t) + 255) & ~(size_t)255;
@@ -480,6 +483,7 @@ moe_status moe_decode_forward_noalloc(const moe_decode_config *cfg, void *stream
     moe_decode_s h{};  // on the stack: no allocation of any kind
     fill_handle(&h, cfg, (char *)base + kScratchCounterBytes);
     h.ws.sync = (int32_t *)base;
+    h.ws.tickets = h.ws.sync + ((size_t)cfg->max_tokens + 1) * kCounterStride + kTicketOff;
     h.synced = 1;
     s = moe_decode_forward(&h, stream, x, n_tokens, router_w, router_bias, expert_w, scales, topk, y, topk_ids,
                            topk_weights);

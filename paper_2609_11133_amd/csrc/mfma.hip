@@ -15,6 +15,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "fp8split.h"
 #include "moe_internal.h"
 
@@ -870,6 +872,466 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 8 ?
     }
 }
 
+// ------------------------------------------------------------------ wide chunks
+//
+// Large batches of FP8 layers: chunks of up to 128 tokens (kWideChunk), so that an
+// expert's weights stream once for nearly all of its tokens; with 32-token chunks a batch
+// of 50 tokens per expert streamed them twice.  HBM bounds these kernels.  One persistent
+// workgroup of eight waves per CU; each wave streams two 16-row tiles (the gate and up
+// rows of the same 16 rows, or two down tiles) against up to eight staged token tiles, so
+// every activation fragment read from LDS feeds two tiles: at 128 tokens the fragment
+// reads of a K block take 2,048 LDS cycles per CU, under the 2,900 that its 32 KB of
+// weights take at the HBM rate.  Items come from a device counter (`ticket`, zeroed by the
+// step's routing), drawn one item ahead, and the weight ring runs on into the next item,
+// so only the first activations of an item are waited for.
+//
+// Measured, us (gate/up and down by the stage events, 32-token chunks -> these): the
+// 480B-shaped layer with biased routing at T=1000 1,845 -> 1,038 and 1,013 -> 564 (5.8 GB
+// and 2.9 GB of weight streams: 5.6 and 5.1 TB/s); uniform routing T=600 1,179 -> 882 and
+// 672 -> 498.  At T=600 the same kernel without its activation staging takes 810 and 454,
+// and without MFMAs 867 and 491: what is left is the staging and, in the down projection,
+// its shorter items.  Four-wave workgroups (two per CU) lost, 934 -> 1,287 at T=600: they
+// stage twice the activations per weight byte.  Items of one expert kept on one XCD lost
+// too (T=1000: down 564 -> 617).
+
+constexpr int kWideW = 8;   // waves per workgroup
+constexpr int kWideArea = 32 * kWideW;  // token rows x K blocks of a segment
+constexpr int kWideNA = 2;  // weight tiles per wave
+constexpr int kWideGrid = 256;  // persistent workgroups: one per CU
+
+// A staged segment: K blocks x token rows = kWideArea,
+// as [hi, lo][token][16-byte pieces, swizzled] codes and [hi, lo][token][E8M0] exponents.
+struct alignas(16) WideSeg {
+    uint8_t code[2][kWideArea * 128];
+    uint8_t ex[2][kWideArea * 4];
+};
+
+// K blocks per segment for NT token tiles.
+template <int NT>
+constexpr int kWideSegK = NT * 16 * 4 <= kWideArea ? 4 : (NT * 16 * 2 <= kWideArea ? 2 : 1);
+
+// Place of 16-byte piece p of token row t: the token XORed into the piece index so that
+// the 16 rows of a fragment read fall on 16 distinct bank groups (a 128-byte row holds
+// half of the banks, so there the token's low bit already picks the half).
+template <int SEGK>
+__device__ inline int wide_place(int p, int t)
+{
+    return SEGK == 1 ? t * 128 + ((p ^ (t >> 1)) & 7) * 16 : t * (SEGK * 128) + ((p & ~15) | ((p ^ t) & 15)) * 16;
+}
+
+// One thread's share of staging a segment: a 16-byte piece of NT*SEGK/4 token rows in both
+// codes, and one 4-byte word of exponents (term tid/kWideArea).  Tokens past the chunk read out
+// of range (zeros, no memory request).  A segment that runs past K stages bytes no block
+// reads.
+template <int NT>
+struct WideStager {
+    static constexpr int SEGK = kWideSegK<NT>, kTok = kWideArea / SEGK;
+    static constexpr int kPieces = SEGK * 8;               // 16-byte pieces of a token row
+    static constexpr int kRows = 64 * kWideW / kPieces;    // token rows per pass
+    static constexpr int Q = 16 * NT / kRows;
+    static_assert(16 * NT % kRows == 0 && kRows % 8 == 0, "whole passes");
+    // rows kRows apart have the same swizzle
+    static constexpr bool kSame = kRows % 16 == 0;
+    uint32_t voff[Q], eoff;
+    int tid, so;
+    u32x4v code[2][Q];
+    uint32_t ex;
+
+    __device__ void init(const int32_t *__restrict__ row_of, int slot0, int mc, int K, int tid_)
+    {
+        tid = tid_;
+        const int p = tid & (kPieces - 1), t0 = tid / kPieces;
+        so = wide_place<SEGK>(p, t0);
+        auto row = [&](int t) { return t < mc ? (uint32_t)(row_of ? row_of[slot0 + t] : slot0 + t) : 0u; };
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int t = kRows * q + t0;
+            voff[q] = t < mc ? row(t) * (uint32_t)K + 16u * p : kOutOfRange;
+        }
+        const int te = (tid / SEGK) & (kTok - 1);
+        eoff = te < mc ? row(te) * (uint32_t)(K / 32) + 4u * (tid & (SEGK - 1)) : kOutOfRange;
+    }
+    __device__ void load(const ActRsrc &B, int sg)
+    {
+        const uint32_t d = (uint32_t)sg * (SEGK * 128), de = (uint32_t)sg * (SEGK * 4);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            code[0][q] = __builtin_amdgcn_raw_buffer_load_b128(B.hi, voff[q] + d, 0, 0);
+            code[1][q] = __builtin_amdgcn_raw_buffer_load_b128(B.lo, voff[q] + d, 0, 0);
+        }
+        ex = __builtin_amdgcn_raw_buffer_load_b32(__builtin_amdgcn_readfirstlane(tid) < kWideArea ? B.ehi : B.elo, eoff + de,
+                                                  0, 0);  // the term is uniform over a wave
+    }
+    __device__ void store(WideSeg &S) const
+    {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                *reinterpret_cast<u32x4v *>(&S.code[h][0] + (kSame ? so + kRows * q * (SEGK * 128) : wide_place<SEGK>(tid & (kPieces - 1), kRows * q + tid / kPieces))) = code[h][q];
+        reinterpret_cast<uint32_t *>(&S.ex[0][0])[tid] = ex;
+    }
+};
+
+// A value that no kernel writes, at an address that is the same for the whole wave: a
+// scalar load.  As a vector load (the compiler cannot prove either once pointers pass
+// from item to item) the block scales made every fourth block wait for all loads in
+// flight.
+__device__ inline float wide_const(const float *p)
+{
+    const uint64_t a = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    return *(const float __attribute__((address_space(4))) *)(((uint64_t)hi << 32) | lo);
+}
+
+// Where a wave's two weight tiles of one item lie: the pointers of wlane and the block
+// scales of its rows.
+struct WideTiles {
+    const uint8_t *arow[kWideNA];
+    const float *sblk[kWideNA];
+};
+
+// The weight ring of a wave, carried from one item to the next.
+struct WideRing {
+    i32x8 A[4][kWideNA];
+};
+
+template <bool PK>
+__device__ inline void wide_load(WideRing &R, int slot, const WideTiles &W, int kb, int g)
+{
+#pragma unroll
+    for (int a = 0; a < kWideNA; ++a) R.A[slot][a] = wfrag<0, PK>(W.arow[a], kb, g);
+}
+
+// An item's first three blocks into ring slots 0..2.
+template <bool PK>
+__device__ inline void wide_fill(WideRing &R, const WideTiles &W, int KB, int lane)
+{
+#pragma unroll
+    for (int u = 0; u < 3; ++u) wide_load<PK>(R, u, W, min(u, KB - 1), lane >> 4);
+}
+
+// Streams this wave's two weight tiles W over KB K blocks against NT staged token tiles;
+// acc[a][j] as in stream_tiles.  All waves of the workgroup call it together; it
+// synchronises them once per staged segment.  On entry the ring holds the item's first
+// three blocks, on return those of the next item (tiles N), so the weight stream does not
+// stop between items.  On return no wave reads `seg` any more.
+template <int NT, bool PK>
+__device__ inline void stream_wide(f32x4 (&acc)[kWideNA][NT], WideRing &R, const WideTiles &W, const WideTiles &N,
+                                   int KB, const ActRsrc &B, WideStager<NT> &st, WideSeg (&seg)[2], int lane)
+{
+    constexpr int NA = kWideNA, SEGK = kWideSegK<NT>;
+    const int r = lane & 15, g = lane >> 4;
+    const int nseg = (KB + SEGK - 1) / SEGK;
+    // block kb of this item, or of the next one past the end (reached only when KB is a
+    // multiple of four, so the ring slots of the two items agree)
+    auto loadA = [&](int slot, int kb) {
+        const bool in = kb < KB;
+        WideTiles S;
+#pragma unroll
+        for (int a = 0; a < NA; ++a) S.arow[a] = in ? W.arow[a] : N.arow[a];
+        wide_load<PK>(R, slot, S, in ? kb : kb - KB, g);
+    };
+    // Token tile j+1's fragments are read from LDS while tile j is multiplied; the
+    // scheduling barriers keep the compiler from hoisting all NT tiles' reads at once,
+    // which does not fit the register file.
+    struct BFrag {
+        i32x8 h, l;
+        int eh, el;
+    };
+    // LDS offsets of this lane's pieces of token row r (tile j adds 16 rows, the low term
+    // half of the codes, a second pair of blocks 256 bytes), written so that only these
+    // few registers hold addresses
+    constexpr int kRow = SEGK * 128;
+    int boff[2][2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) boff[kk][q] = wide_place<SEGK>((8 * kk + 4 * q + g) & (8 * SEGK - 1), r);
+    const int xoff = r * (SEGK * 4) + g;
+    auto readB = [&](BFrag &f, const WideSeg &S, int kk, int j) {
+        const uint8_t *c = &S.code[0][0] + 16 * j * kRow + (kk >> 1) * 256;
+        const uint8_t *x = &S.ex[0][0] + xoff + 16 * j * (SEGK * 4) + 4 * kk;
+        const u32x4v h0 = *reinterpret_cast<const u32x4v *>(c + boff[kk & 1][0]);
+        const u32x4v h1 = *reinterpret_cast<const u32x4v *>(c + boff[kk & 1][1]);
+        const u32x4v l0 = *reinterpret_cast<const u32x4v *>(c + boff[kk & 1][0] + sizeof(S.code[0]));
+        const u32x4v l1 = *reinterpret_cast<const u32x4v *>(c + boff[kk & 1][1] + sizeof(S.code[0]));
+        f.h = (i32x8){(int)h0.x, (int)h0.y, (int)h0.z, (int)h0.w, (int)h1.x, (int)h1.y, (int)h1.z, (int)h1.w};
+        f.l = (i32x8){(int)l0.x, (int)l0.y, (int)l0.z, (int)l0.w, (int)l1.x, (int)l1.y, (int)l1.z, (int)l1.w};
+        f.eh = x[0];
+        f.el = x[sizeof(S.ex[0])];
+    };
+    auto compute = [&](int slot, const WideSeg &S, int kk, int kb) {
+        float sc[NA];
+#pragma unroll
+        for (int a = 0; a < NA; ++a) sc[a] = wide_const(W.sblk[a] + kb);
+        BFrag f[2];
+        readB(f[0], S, kk, 0);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            if (j + 1 < NT) readB(f[(j + 1) & 1], S, kk, j + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int a = 0; a < NA; ++a)
+                mma2<0>(acc[a][j], R.A[slot][a], 127, sc[a], f[j & 1].h, f[j & 1].eh, f[j & 1].l, f[j & 1].el);
+        }
+    };
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[a][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    st.load(B, 0);
+    st.store(seg[0]);
+    st.load(B, min(1, nseg - 1));
+    sync_lds();
+    int kb = 0;
+    for (; kb + 4 <= KB; kb += 4) {  // four blocks per iteration: 4 / SEGK segments
+        const int sg = kb / SEGK;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            loadA((u + 3) & 3, KB % 4 ? min(kb + u + 3, KB - 1) : kb + u + 3);
+            __builtin_amdgcn_sched_barrier(0);
+            const int b = SEGK == 4 ? sg & 1 : (u / SEGK) & 1;  // the block's buffer
+            compute(u, seg[b], u % SEGK, kb + u);
+            if ((u + 1) % SEGK == 0) {
+                st.store(seg[b ^ 1]);
+                st.load(B, min(sg + 2 + u / SEGK, nseg - 1));
+                sync_lds();
+            }
+        }
+    }
+    // Fewer than four blocks remain, in ring slots 0..2; their first segment is staged, the
+    // next one sits in the stager's registers.
+    if (kb < KB) {
+        const int sg = kb / SEGK;
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            if (kb + u < KB) {
+                const int b = SEGK == 4 ? sg & 1 : (u / SEGK) & 1;
+                if (u && u % SEGK == 0) {
+                    st.store(seg[b]);
+                    st.load(B, min(sg + 1 + u / SEGK, nseg - 1));
+                    sync_lds();
+                }
+                compute(u, seg[b], u % SEGK, kb + u);
+            }
+        }
+        sync_lds();
+        wide_fill<PK>(R, N, KB, lane);
+    }
+}
+
+// gate/up: item = (chunk, 16 * kWideW rows of the intermediate dimension); wave w streams the
+// gate and the up rows i0 + 16w .. +16, so silu(g)*u forms in its registers; waves 2q and
+// 2q+1 share the 32-row group of h's split and exchange their column maxima through LDS
+// (over seg[1], which the next item first writes after its first barrier).
+template <bool PK>
+__device__ inline void w13_wide_tiles(WideTiles &W, const uint8_t *__restrict__ we, const uint8_t *__restrict__ se,
+                                      int H, int I, int r0, int lane)
+{
+    const size_t rowb = (size_t)H;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const int row0 = a * I + r0;
+        W.arow[a] = wlane<PK>(we, row0, rowb, lane);
+        W.sblk[a] = (const float *)se + (size_t)(row0 / 128) * (H / 128);
+    }
+}
+
+template <int NT, bool PK>
+__device__ inline void w13_item_wide(WideRing &R, const WideTiles &W, const WideTiles &N, int H, int I, int r0,
+                                     int slot0, int mc, const int *tok, const ActRsrc &X, uint8_t *__restrict__ hs_hi,
+                                     uint8_t *__restrict__ hs_lo, uint8_t *__restrict__ he_hi,
+                                     uint8_t *__restrict__ he_lo, WideSeg (&seg)[2], int wave, int lane, int tid)
+{
+    const int r = lane & 15, g = lane >> 4;
+    WideStager<NT> st;
+    st.init(tok, 0, mc, H, tid);
+    f32x4 acc[2][NT];
+    stream_wide<NT, PK>(acc, R, W, N, H / 128, X, st, seg, lane);
+    float *s_am = reinterpret_cast<float *>(&seg[1].code[0][0]), *s_rm = s_am + kWideW * NT * 16;
+    static_assert(sizeof(float) * 2 * kWideW * 8 * 16 <= sizeof(seg[1].code), "exchange buffers");
+    auto ix = [&](int w, int j) { return (w * NT + j) * 16 + r; };
+    float h[NT][4], res[NT][4], am[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float gi = acc[0][j][i];
+            h[j][i] = gi / (1.0f + expf(-gi)) * acc[1][j][i];
+        }
+        float m = amax_of(h[j]);
+        m = fmaxf(m, __shfl_xor(m, 16));
+        am[j] = fmaxf(m, __shfl_xor(m, 32));
+        if (g == 0) s_am[ix(wave, j)] = am[j];
+    }
+    sync_lds();
+    int ch[NT];
+    uint32_t qh[NT][1], ql[1];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        ch[j] = exp_for_group(fmaxf(am[j], s_am[ix(wave ^ 1, j)]));
+        split_hi(h[j], ch[j], qh[j], res[j]);
+        float m = amax_of(res[j]);
+        m = fmaxf(m, __shfl_xor(m, 16));
+        am[j] = fmaxf(m, __shfl_xor(m, 32));
+        if (g == 0) s_rm[ix(wave, j)] = am[j];
+    }
+    sync_lds();
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const int cl = exp_for_group(fmaxf(am[j], s_rm[ix(wave ^ 1, j)]));
+        split_lo(res[j], cl, ql);
+        if (16 * j + r < mc) {
+            const size_t slot = (size_t)slot0 + 16 * j + r;
+            *reinterpret_cast<uint32_t *>(hs_hi + slot * I + r0 + 4 * g) = qh[j][0];
+            *reinterpret_cast<uint32_t *>(hs_lo + slot * I + r0 + 4 * g) = ql[0];
+            if ((wave & 1) == 0 && g == 0) {
+                he_hi[slot * (I / 32) + r0 / 32] = (uint8_t)ch[j];
+                he_lo[slot * (I / 32) + r0 / 32] = (uint8_t)cl;
+            }
+        }
+    }
+}
+
+// A chunk record, the same for every lane, in scalar registers.
+__device__ inline int4 wide_rec(const int4 *recs, int i)
+{
+    const int4 r = recs[i];
+    return make_int4(__builtin_amdgcn_readfirstlane(r.x), __builtin_amdgcn_readfirstlane(r.y),
+                     __builtin_amdgcn_readfirstlane(r.z), 0);
+}
+
+// Calls go(integral_constant NT) with the token tiles of a chunk of mc tokens.
+template <class F>
+__device__ inline void wide_tiles_of(int mc, F go)
+{
+    if (mc > 96) go(std::integral_constant<int, 8>{});
+    else if (mc > 64) go(std::integral_constant<int, 6>{});
+    else if (mc > 32) go(std::integral_constant<int, 4>{});
+    else go(std::integral_constant<int, 2>{});
+}
+
+template <bool PK>
+__global__ __launch_bounds__(64 * kWideW) __attribute__((amdgpu_waves_per_eu(2))) void w13_wide_kernel(
+    const uint8_t *__restrict__ ew, const uint8_t *__restrict__ es, const int32_t *__restrict__ meta,
+    const int32_t *__restrict__ tok_of, const uint8_t *__restrict__ xs_hi, const uint8_t *__restrict__ xs_lo,
+    const uint8_t *__restrict__ xe_hi, const uint8_t *__restrict__ xe_lo, uint8_t *__restrict__ hs_hi,
+    uint8_t *__restrict__ hs_lo, uint8_t *__restrict__ he_hi, uint8_t *__restrict__ he_lo, int32_t *ticket, int T,
+    int H, int I, int E, size_t ewb, size_t esb)
+{
+    __shared__ WideSeg seg[2];
+    __shared__ int s_tok[2][kWideChunk];  // token rows of this item's chunk and the next one's
+    __shared__ int s_next;
+    const MetaIdx mi{E};
+    const int tiles = I / (16 * kWideW);
+    const int4 *recs = reinterpret_cast<const int4 *>(meta + mi.chunk_rec());
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const ActRsrc X = act_rsrc(xs_hi, xs_lo, xe_hi, xe_lo, (uint32_t)T, (uint32_t)H);
+    auto row0 = [&](int it) { return (it % tiles) * (16 * kWideW) + 16 * wave; };
+    const int n_items = meta[mi.n_mfma_chunks()] * tiles;
+    int item = blockIdx.x, nxt = item + gridDim.x;
+    if (item >= n_items) return;  // uniform over the workgroup
+    int4 rec = wide_rec(recs, item / tiles);  // {expert, first slot, tokens, -}
+    WideTiles W, N;
+    w13_wide_tiles<PK>(W, ew + (size_t)rec.x * ewb, es + (size_t)rec.x * esb, H, I, row0(item), lane);
+    WideRing R;
+    wide_fill<PK>(R, W, H / 128, lane);
+    if (tid < kWideChunk) s_tok[0][tid] = tid < rec.z ? tok_of[rec.y + tid] : 0;
+    __syncthreads();
+    for (int p = 0;; p ^= 1) {
+        const int after = tid == 0 ? atomicAdd(ticket, 1) + 2 * (int)gridDim.x : 0;
+        const bool more = nxt < n_items;
+        const int ni = more ? nxt : item;  // after the last item: its own blocks again
+        const int4 nrec = wide_rec(recs, ni / tiles);
+        const int ntok = tid < nrec.z && tid < kWideChunk ? tok_of[nrec.y + tid] : 0;
+        w13_wide_tiles<PK>(N, ew + (size_t)nrec.x * ewb, es + (size_t)nrec.x * esb, H, I, row0(ni), lane);
+        wide_tiles_of(rec.z, [&](auto nt) {
+            w13_item_wide<decltype(nt)::value, PK>(R, W, N, H, I, row0(item), rec.y, rec.z, s_tok[p], X, hs_hi,
+                                                        hs_lo, he_hi, he_lo, seg, wave, lane, tid);
+        });
+        if (!more) return;
+        if (tid < kWideChunk) s_tok[p ^ 1][tid] = ntok;
+        if (tid == 0) s_next = after;
+        sync_lds();
+        item = nxt;
+        nxt = __builtin_amdgcn_readfirstlane(s_next);
+        rec = nrec;
+        W = N;
+    }
+}
+
+// down: item = (chunk, 32 * kWideW output rows); wave w streams rows n0 + 32w .. +32 as two tiles.
+template <bool PK>
+__device__ inline void w2_wide_tiles(WideTiles &W, const uint8_t *__restrict__ we, const uint8_t *__restrict__ se,
+                                     int H, int I, int r0, int lane)
+{
+    const size_t rowb = (size_t)I;
+    const uint8_t *we2 = we + (size_t)2 * I * H;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const int row0 = r0 + 16 * a;
+        W.arow[a] = wlane<PK>(we2, row0, rowb, lane);
+        W.sblk[a] = (const float *)se + (size_t)2 * (I / 128) * (H / 128) + (size_t)(row0 / 128) * (I / 128);
+    }
+}
+
+template <bool PK>
+__global__ __launch_bounds__(64 * kWideW) __attribute__((amdgpu_waves_per_eu(2))) void w2_wide_kernel(
+    const uint8_t *__restrict__ ew, const uint8_t *__restrict__ es, const int32_t *__restrict__ meta,
+    const uint8_t *__restrict__ hs_hi, const uint8_t *__restrict__ hs_lo, const uint8_t *__restrict__ he_hi,
+    const uint8_t *__restrict__ he_lo, float *__restrict__ obuf, int32_t *ticket, int P, int H, int I, int E,
+    size_t ewb, size_t esb)
+{
+    __shared__ WideSeg seg[2];
+    __shared__ int s_next;
+    const MetaIdx mi{E};
+    const int tiles = H / (32 * kWideW);
+    const int4 *recs = reinterpret_cast<const int4 *>(meta + mi.chunk_rec());
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const ActRsrc Hs = act_rsrc(hs_hi, hs_lo, he_hi, he_lo, (uint32_t)P, (uint32_t)I);
+    auto row0 = [&](int it) { return (it % tiles) * (32 * kWideW) + 32 * wave; };
+    const int n_items = meta[mi.n_mfma_chunks()] * tiles;
+    int item = blockIdx.x, nxt = item + gridDim.x;
+    if (item >= n_items) return;  // uniform over the workgroup
+    int4 rec = wide_rec(recs, item / tiles);
+    WideTiles W, N;
+    w2_wide_tiles<PK>(W, ew + (size_t)rec.x * ewb, es + (size_t)rec.x * esb, H, I, row0(item), lane);
+    WideRing R;
+    wide_fill<PK>(R, W, I / 128, lane);
+    for (;;) {
+        const int after = tid == 0 ? atomicAdd(ticket, 1) + 2 * (int)gridDim.x : 0;
+        const bool more = nxt < n_items;
+        const int ni = more ? nxt : item;  // after the last item: its own blocks again
+        const int4 nrec = wide_rec(recs, ni / tiles);
+        w2_wide_tiles<PK>(N, ew + (size_t)nrec.x * ewb, es + (size_t)nrec.x * esb, H, I, row0(ni), lane);
+        wide_tiles_of(rec.z, [&](auto nt) {
+            constexpr int NT = decltype(nt)::value;
+            WideStager<NT> st;
+            st.init(nullptr, rec.y, rec.z, I, tid);
+            f32x4 acc[2][NT];
+            stream_wide<NT, PK>(acc, R, W, N, I / 128, Hs, st, seg, lane);
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                if (16 * j + r < rec.z) {
+                    const size_t slot = (size_t)rec.y + 16 * j + r;
+#pragma unroll
+                    for (int a = 0; a < 2; ++a)
+                        *reinterpret_cast<f32x4 *>(obuf + slot * H + row0(item) + 16 * a + 4 * g) = acc[a][j];
+                }
+        });
+        if (!more) return;
+        if (tid == 0) s_next = after;
+        sync_lds();
+        item = nxt;
+        nxt = __builtin_amdgcn_readfirstlane(s_next);
+        rec = nrec;
+        W = N;
+    }
+}
+
 // Waves per workgroup of the staged kernels.  FP8 weights stream at 4 waves and two
 // workgroups per CU: eight waves per CU hold the HBM stream at its best, and more
 // waves per CU slowed it (the 235B- and 480B-shaped layers lost 9-18%).  E2M1
@@ -909,7 +1371,8 @@ int mfma_grid(const Layer &L, int T, int k, int items_per_chunk, int per_block)
 {
     const long pairs = (long)T * k;
     const long recs = pairs < L.E ? pairs : L.E;
-    const long chunks = recs + (pairs + kMfmaChunk - 1) / kMfmaChunk;  // >= number of chunk records
+    const int chunk = chunk_tokens(L, T, k);
+    const long chunks = recs + (pairs + chunk - 1) / chunk;  // >= number of chunk records
     const long blocks = (chunks * items_per_chunk + per_block - 1) / per_block;
     return blocks < 1 ? 1 : (blocks > 65535 ? 65535 : (int)blocks);
 }
@@ -940,6 +1403,12 @@ template <int FMT, bool PK>
 hipError_t w13_launch(const Layer &L, const uint8_t *ew, const uint8_t *es, int T, int k, const int32_t *meta,
                       const int32_t *tok_of, const Workspace &ws, hipStream_t st)
 {
+    if (FMT == 0 && chunk_tokens(L, T, k) == kWideChunk) {
+        w13_wide_kernel<PK><<<kWideGrid, 64 * kWideW, 0, st>>>(
+            ew, es, meta, tok_of, ws.xs_hi, ws.xs_lo, ws.xe_hi, ws.xe_lo, ws.hs_hi, ws.hs_lo, ws.he_hi, ws.he_lo,
+            ws.tickets, T, L.H, L.I, L.E, L.expert_w_bytes, L.expert_s_bytes);
+        return hipGetLastError();
+    }
     if ((L.H / 128) % 4 == 0) {
         if constexpr (FMT == 1 && PK)
             if (w13_three_tiles<FMT, PK>(L))
@@ -957,6 +1426,12 @@ template <int FMT, bool PK>
 hipError_t w2_launch(const Layer &L, const uint8_t *ew, const uint8_t *es, int T, int k, const int32_t *meta,
                      const Workspace &ws, hipStream_t st)
 {
+    if (FMT == 0 && chunk_tokens(L, T, k) == kWideChunk) {
+        w2_wide_kernel<PK><<<kWideGrid, 64 * kWideW, 0, st>>>(
+            ew, es, meta, ws.hs_hi, ws.hs_lo, ws.he_hi, ws.he_lo, ws.o, ws.tickets + 1, T * k, L.H, L.I, L.E,
+            L.expert_w_bytes, L.expert_s_bytes);
+        return hipGetLastError();
+    }
     // Staging pays a per-item prologue; with fewer than 16 K blocks per row (I < 2048)
     // the two-tile kernel measured faster for FP8 weights (235B-shaped layer: 155
     // against 160 us at T=64).  E2M1 weights carry half the bytes per activation
@@ -1063,6 +1538,20 @@ __global__ void pack_scales_kernel(const uint8_t *__restrict__ src, uint8_t *__r
 }
 
 }  // namespace
+
+// Token rows of a step's chunk records (MFMA experts): 128 for FP8 layers once an expert has
+// enough tokens on average for the streams saved to outweigh the wide kernels' item
+// starts, which weigh more the shorter the down projection's rows (I) are.  Packed,
+// step us (32-token chunks / wide): 480B-shaped (I 2560) 6.4 pairs per expert 1,240 /
+// 1,253, 12.8 1,338 / 1,279; 235B-shaped (I 1536) 12 468 / 473, 16 503 / 485, 24 587 /
+// 519; I 1024: 18 119 / 125, 24 142 / 138; I 640: 19 453 / 470, 32 669 / 536; I 384: 32
+// 70 / 85, 80 125 / 119.  Row-major weights: I 1536, 8 512 / 580, 16 600 / 608.
+int chunk_tokens(const Layer &L, int T, int k)
+{
+    if (L.wfmt != 0 || L.H % (32 * kWideW)) return kMfmaChunk;
+    const long work = (long)T * k * L.I, line = L.wlayout ? 20000 : 26000;
+    return work > line * L.E ? kWideChunk : kMfmaChunk;
+}
 
 hipError_t launch_w13_mfma(const Layer &L, const void *expert_w, const void *scales, int T, int k,
                            const int32_t *meta, const int32_t *tok_of, const Workspace &ws, hipStream_t st)

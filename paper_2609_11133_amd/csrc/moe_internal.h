@@ -18,6 +18,7 @@ struct Workspace {
     float *h;          // [Tmax*kmax][I] SwiGLU activations per slot (GEMV path)
     float *o;          // [Tmax*kmax][H] expert outputs per slot
     int32_t *sync;     // [(Tmax + 2) * kCounterStride] routing counters (zero between launches)
+    int32_t *tickets;  // [2] item counters of the large-batch kernels (in sync, zeroed by the grouping)
     uint8_t *xs_hi, *xs_lo;  // [Tmax][H] 2-term FP8 split of x (MFMA path)
     uint8_t *xe_hi, *xe_lo;  // [Tmax][H/32] E8M0 exponents of the split
     uint8_t *hs_hi, *hs_lo;  // [Tmax*kmax][I] 2-term FP8 split of h (MFMA path)
@@ -33,8 +34,8 @@ struct Workspace {
 
 // Layout of the meta block (int32 words).  Records are int4 and start on 16-byte
 // boundaries: GEMV records {expert, first slot, tokens, 0}; MFMA chunk records
-// {expert, first slot of the chunk, tokens in the chunk (<= 32), 0}, one per 32
-// tokens of an MFMA expert.
+// {expert, first slot of the chunk, tokens in the chunk, 0}, one per chunk_tokens()
+// (at least 32) tokens of an MFMA expert.
 struct MetaIdx {
     int E;
     int max_chunks;  // E + ceil(Tmax * kmax / 32) bounds the number of MFMA chunks
@@ -54,11 +55,13 @@ struct MetaIdx {
 
 __host__ __device__ inline int max_mfma_chunks(int E, int Tmax, int kmax) { return E + (Tmax * kmax + 31) / 32; }
 
-constexpr int kMfmaChunk = 32;      // tokens per MFMA pass (two 16-column tiles)
+constexpr int kMfmaChunk = 32;   // tokens of a chunk record (two 16-column tiles)
+constexpr int kWideChunk = 128;  // tokens of a chunk record of the large-batch kernels
 // Screened routing by default from T*E*H >= 2^26 multiply-adds of exact logits: below
 // it the fixed costs of the extra pass outweigh the logits it saves.
 constexpr long kScreenMinMacs = 1L << 26;
 constexpr int kCandCounterOff = 32;  // int32 words from the fallback counter to the candidate counter
+constexpr int kTicketOff = 48;       // ... and to the item counters of the large-batch kernels
 
 // K slices of the screened routing's partial sums: at most 16 and H/256, and the
 // partials at most 4 Mi fp64 pairs (64 MB); 0 when H is not a multiple of 256.
@@ -109,10 +112,13 @@ struct RouteParams {
     int mstar;
     int do_group;
     int max_chunks;
+    int chunk;   // tokens per MFMA chunk record (chunk_tokens)
     int screen;  // 1: screened routing for this step (forward with grouping only)
 };
 
 // ---- launchers (all enqueue on `st`, return hipGetLastError())
+// Tokens per MFMA chunk record of a step: kMfmaChunk or kWideChunk.
+int chunk_tokens(const Layer &L, int T, int k);
 hipError_t launch_zero(int32_t *p, int n, hipStream_t st);
 hipError_t launch_route(const Layer &L, const RouteParams &P, hipStream_t st);
 hipError_t launch_pack_weights(const Layer &L, const void *src, void *dst, int n_experts, hipStream_t st);

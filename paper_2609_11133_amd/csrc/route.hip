@@ -528,7 +528,7 @@ struct RouteArgs {
     uint8_t *xs_hi, *xs_lo, *xe_hi, *xe_lo;  // activation split (NULL: MFMA path off)
     _Float16 *x16;                           // f16 copy of x * 2^-k (NULL: none)
     int32_t *xk;                             // [T] the token's k
-    int T, E, H, k, epw, bpt, mstar, do_group, max_chunks;
+    int T, E, H, k, epw, bpt, mstar, do_group, max_chunks, chunk;
     int id_cache;  // the grouping keeps the choices in LDS (sized by the launch)
     // screened routing (large T): per K slice ks, partial sums part[ks][t][e] =
     // (sum x*w, sum |x*w|) and the slice's max |x[t,.]|, max |w[e,.]|
@@ -661,7 +661,7 @@ __device__ __attribute__((always_inline)) inline void group_pairs(const RouteArg
             if (c > 0) {
                 if (A.mstar > 0 && c >= A.mstar) {
                     v[2]++;
-                    v[3] += (c + kMfmaChunk - 1) / kMfmaChunk;
+                    v[3] += (c + A.chunk - 1) / A.chunk;
                 } else {
                     v[1]++;
                 }
@@ -680,8 +680,8 @@ __device__ __attribute__((always_inline)) inline void group_pairs(const RouteArg
             if (c > 0) {
                 if (A.mstar > 0 && c >= A.mstar) {
                     int4 *cr = reinterpret_cast<int4 *>(A.meta + mi.chunk_rec());
-                    for (int m0 = 0; m0 < c; m0 += kMfmaChunk)
-                        cr[v[3]++] = make_int4(e, v[0] + m0, min(kMfmaChunk, c - m0), 0);
+                    for (int m0 = 0; m0 < c; m0 += A.chunk)
+                        cr[v[3]++] = make_int4(e, v[0] + m0, min(A.chunk, c - m0), 0);
                     v[2]++;
                 } else {
                     reinterpret_cast<int4 *>(A.meta + mi.gemv_rec())[v[1]++] = make_int4(e, v[0], c, 0);
@@ -700,6 +700,7 @@ __device__ __attribute__((always_inline)) inline void group_pairs(const RouteArg
         A.meta[mi.n_exact()] = n_exact;
         A.meta[mi.screened()] = A.KS ? 1 : 0;
         st_dev(A.cnt_all, 0);
+        A.fb_acc[kTicketOff] = A.fb_acc[kTicketOff + 1] = 0;
     }
     __syncthreads();
     for (int p = threadIdx.x; p < P; p += blockDim.x) {
@@ -1091,6 +1092,7 @@ hipError_t launch_route(const Layer &L, const RouteParams &P, hipStream_t st)
     A.mstar = P.mstar;
     A.do_group = P.do_group;
     A.max_chunks = P.max_chunks;
+    A.chunk = P.chunk;
     A.part = (double2 *)P.part;
     A.xmax = P.xmax;
     A.wmax = P.wmax;

@@ -492,6 +492,36 @@ def test_packed_mxfp4_skewed_chunks(dev, cfg, T):
         assert max(counts) > 64
 
 
+# The large-batch FP8 kernels (128-token chunks): K block counts of 6 and 5 (gate/up, down:
+# tails of two and one blocks), and of 4 and 3.
+WIDE_FP8 = [LayerConfig("wide-k6-5", 768, 8, 2, 640, "bf16", "bf16", "fp8", "zipf:1.1", []),
+            LayerConfig("wide-k4-3", 512, 8, 2, 384, "f32", "bf16", "fp8", "zipf:1.1", [])]
+
+
+@pytest.mark.parametrize("cfg", WIDE_FP8, ids=lambda c: c.name)
+@pytest.mark.parametrize("layout", [0, 1], ids=["rows", "packed"])
+def test_wide_chunks(dev, cfg, layout):
+    """FP8 layers on both sides of the switch to 128-token chunks (T*k*I above 20,000 per
+    expert packed, 26,000 row-major).  The Zipf-skewed batches give chunks of few tokens, of
+    every number of token-tile pairs (2, 4, 6, 8 tiles) and, at the largest, several chunks
+    of one expert."""
+    hl = W.host_layer(cfg, seed=611)
+    edge = (26000 if layout == 0 else 20000) * cfg.n_experts // (cfg.topk * cfg.inter)
+    run = Run(cfg, hl, dev, max_tokens=700, weight_layout=layout)
+    sizes = set()
+    for T in (edge, edge + 1, 340, 700):
+        check_layer(run, W.host_x(cfg, T, seed=611 + T), label=f"{cfg.name} T={T}")
+        _, counts = run.m.stats()
+        say(f"[wide] {cfg.name} T={T}: tokens per expert {sorted(counts, reverse=True)}")
+        if T > edge:
+            for c in counts:
+                sizes |= {128} if c >= 128 else set()
+                sizes |= {c % 128} - {0}
+    assert max(counts) > 256
+    for lo, hi in ((1, 32), (33, 64), (65, 96), (97, 128)):
+        assert any(lo <= n <= hi for n in sizes), (lo, hi, sorted(sizes))
+
+
 PK_NV_WIDE = LayerConfig("pk-nv-wide", 1024, 16, 8, 1024, "bf16", "bf16", "nvfp4", "zipf:1.1", [])
 
 
