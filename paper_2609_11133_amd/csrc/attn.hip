@@ -17,8 +17,8 @@
 // partials add directly; it writes (max, sum, O) of its split, and the splits of each
 // (sequence, query head) are merged in split order: by the last of the sequence's
 // workgroups for that key/value head (a device-scope counter, the partials written and
-// read with device-coherent accesses) when a sequence has at most kFusedSplits splits,
-// else by a second kernel.  A sequence with one split writes its output directly.
+// read with device-coherent accesses), or by a second kernel where the configuration asks
+// for it.  A sequence with one split writes its output directly.
 //
 // Operand layout of v_mfma_f32_16x16x32_bf16 (checked on the device): lane l holds
 // row/column l%16 and K [8g, 8g+8) with g = l/16; the result gives lane l rows
@@ -30,6 +30,8 @@
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
+
+#include <type_traits>
 
 #include "../../include/attn_decode.h"
 
@@ -52,7 +54,9 @@ constexpr int kChunk = kWaves * kWaveTok;  // tokens per split
 constexpr int kDT = kD / 16;               // 16-column tiles of the output
 constexpr float kLog2e = 1.44269504088896340736f;
 constexpr int kRawBufferWord3 = 0x00020000;  // untyped 32-bit data format, no swizzle
-constexpr int kFusedSplits = 16;             // splits merged inside the split kernel, at most
+constexpr int kFusedSplits = 32;             // splits merged inside the split kernel, at most
+constexpr long kGridWorkgroups = 3072;       // workgroups up to which the grid takes more splits
+constexpr int kUserSplits = 16;              // ... and at most by fused_merge_max_splits
 
 // Device-coherent accesses for the hand-off between workgroups (relaxed atomics at agent
 // scope bypass the per-XCD L2), and a wait for this thread's stores.
@@ -80,11 +84,21 @@ __device__ inline __amdgpu_buffer_rsrc_t rsrc(const void *base, uint32_t bytes)
 __device__ inline bf16x8 as_bf16x8(const u32x4v &u) { return __builtin_bit_cast(bf16x8, u); }
 
 // Split kernel: partial (max, sum, O) of one 256-token split for one (sequence, key/value
-// head) and its query heads.  Grid (splits, Hkv, B), 256 threads.  Scores are kept in
+// head) and its query heads.  Grid (Hkv, B, splits), 256 threads.  Scores are kept in
 // log2 units (scale * log2 e folded in), so p = exp2(s - m).  A split is R consecutive
-// chunks (online softmax across them); with FUSED each sequence sets its own R.  FUSED: the merge of the splits happens here
-// (S <= kFusedSplits; `cnt` holds one zeroed counter per (b, g), left at zero again), and
-// `out` is written here.
+// chunks (online softmax across them); with FUSED each sequence sets its own R.  FUSED: the
+// merge of the splits happens here (the grid has at most kFusedSplits; `cnt` holds one
+// zeroed counter per (b, g), left at zero again), and `out` is written here.
+//
+// At short contexts the latency chain of one workgroup bounds the step (length, page
+// table, keys and values, merge), and most workgroups of the grid have nothing to do.  The
+// split index is the slowest of the grid, so that every sequence's first splits start at
+// once and the idle workgroups pass through the slots they leave; with the split index
+// fastest the idle ones of each sequence held the slots (two per CU) before the next
+// sequence's work.  Step us, fastest / slowest: 24 sequences of 64 tokens on 4 heads 13.2 /
+// 9.3, of 512 23.7 / 11.7, of 2048 30.4 / 26.4, of 32768 290 / 288.  (A grid of at most
+// 1024 workgroups that look their items up in the batch's lengths has no idle ones, but
+// the look-up added 2.4 us to every workgroup's chain.)
 template <bool FUSED>
 __global__ __launch_bounds__(256) void attn_split_kernel(const uint16_t *__restrict__ q,
                                                          const uint16_t *__restrict__ kc,
@@ -99,13 +113,17 @@ __global__ __launch_bounds__(256) void attn_split_kernel(const uint16_t *__restr
     __shared__ f32x4 red[kWaves][kDT][64];
     __shared__ float s_w[FUSED ? kFusedSplits : 1][16], s_den[16];
     __shared__ int s_last;
-    const int c = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
+    const int c = blockIdx.z, g = blockIdx.x, b = blockIdx.y;
     const int L = min(max(ctx[b], 0), max_pages * kP);
-    // FUSED: each sequence spreads its own chunks over the S splits of the grid, at least
-    // one chunk per split (R = ceil(chunks / S), at most the configuration's R): a short
+    // FUSED: a sequence of at most `slots` chunks (the grid's splits) takes one split per
+    // chunk, a longer one spreads its chunks over the configuration's S splits.  So a short
     // context in a configuration sized for long ones still gets one workgroup per chunk,
     // and a sequence's result depends on its own length only, never on its batch.
-    if (FUSED) R = max(1, ((L + kChunk - 1) / kChunk + S - 1) / S);
+    const int slots = gridDim.z;  // partials per (b, g)
+    if (FUSED) {
+        const int nc = (L + kChunk - 1) / kChunk;
+        R = nc <= slots ? 1 : (nc + S - 1) / S;
+    }
     const int t0 = c * R * kChunk;  // first token of this split
     const int tid = threadIdx.x, lane = tid & 63;
     uint16_t *orow = out + ((size_t)b * Hkv + g) * G * kD;  // the group's [G][D] outputs
@@ -262,7 +280,7 @@ __global__ __launch_bounds__(256) void attn_split_kernel(const uint16_t *__restr
         }
         return;
     }
-    const size_t part0 = ((size_t)b * Hkv + g) * S, part = part0 + c;
+    const size_t part0 = ((size_t)b * Hkv + g) * slots, part = part0 + c;
 #pragma unroll
     for (int k = 0; k < 16 * kD / 256; ++k) {
         const int e = tid + 256 * k;  // (head n, dim d)
@@ -311,11 +329,21 @@ __global__ __launch_bounds__(256) void attn_split_kernel(const uint16_t *__restr
         // weights 2^(m_c - M) and the denominator per head, splits in ascending order
         if (tid < 16) {
             float mc[kFusedSplits], lc[kFusedSplits];
+            auto load_ml = [&](auto first) {
 #pragma unroll
-            for (int cc = 0; cc < kFusedSplits; ++cc) {
-                const size_t pc = (part0 + min(cc, ns - 1)) * 16 + tid;
-                mc[cc] = ld_dev(&pml[pc * 2]);
-                lc[cc] = ld_dev(&pml[pc * 2 + 1]);
+                for (int u = 0; u < kFusedSplits / 2; ++u) {
+                    constexpr int c0 = decltype(first)::value;
+                    const size_t pc = (part0 + min(c0 + u, ns - 1)) * 16 + tid;
+                    mc[c0 + u] = ld_dev(&pml[pc * 2]);
+                    lc[c0 + u] = ld_dev(&pml[pc * 2 + 1]);
+                }
+            };
+            load_ml(std::integral_constant<int, 0>{});
+            if (ns > kFusedSplits / 2) {
+                load_ml(std::integral_constant<int, kFusedSplits / 2>{});
+            } else {
+#pragma unroll
+                for (int u = kFusedSplits / 2; u < kFusedSplits; ++u) mc[u] = mc[0], lc[u] = 0.f;
             }
             float M = -INFINITY;
 #pragma unroll
@@ -424,8 +452,8 @@ int check_config(const attn_decode_config *c)
     if (!c) return fail(ATTN_ERR_INVALID, "config is NULL");
     for (int i = 0; i < 3; ++i)
         if (c->reserved[i] != 0) return fail(ATTN_ERR_INVALID, "config.reserved[%d] must be zero", i);
-    if (c->fused_merge_max_splits > kFusedSplits)
-        return fail(ATTN_ERR_INVALID, "fused_merge_max_splits=%d exceeds %d", c->fused_merge_max_splits, kFusedSplits);
+    if (c->fused_merge_max_splits > kUserSplits)
+        return fail(ATTN_ERR_INVALID, "fused_merge_max_splits=%d exceeds %d", c->fused_merge_max_splits, kUserSplits);
     if (c->n_kv_heads < 1) return fail(ATTN_ERR_INVALID, "n_kv_heads=%d must be positive", c->n_kv_heads);
     if (c->n_q_heads < 1 || c->n_q_heads % c->n_kv_heads)
         return fail(ATTN_ERR_INVALID, "n_q_heads=%d must be a positive multiple of n_kv_heads=%d", c->n_q_heads,
@@ -444,6 +472,16 @@ int check_config(const attn_decode_config *c)
 
 int max_splits(const attn_decode_config *c) { return (c->max_pages_per_seq * kP + kChunk - 1) / kChunk; }
 
+// Splits per sequence merged in the split kernel, at most: the configuration's, or by
+// default 16, and 32 where 16 would leave CUs without a workgroup however long the
+// contexts are (fewer than 16 (sequence, key/value head) rows on 256 CUs: one sequence of
+// 32K tokens on 4 heads 42.7 -> 30.6 us, four on 2 heads 49.2 -> 40.0).
+int split_limit(const attn_decode_config *c)
+{
+    if (c->fused_merge_max_splits > 0) return c->fused_merge_max_splits;
+    return (long)c->n_kv_heads * c->max_batch < 16 ? kFusedSplits : kUserSplits;
+}
+
 // Partials per (sequence, key/value head) the workspace holds: every 256-token chunk's
 // when the second kernel merges; with the merge in the split kernel at most the split
 // limit (the grid's S never exceeds it, whatever the device), so the workspace does not
@@ -452,7 +490,7 @@ int partial_slots(const attn_decode_config *c)
 {
     const int sf = max_splits(c);
     if (c->fused_merge_max_splits < 0) return sf;
-    const int lim = c->fused_merge_max_splits == 0 ? kFusedSplits : c->fused_merge_max_splits;
+    const int lim = split_limit(c);
     return sf < lim ? sf : lim;
 }
 
@@ -468,7 +506,6 @@ size_t partial_ml_bytes(const attn_decode_config *c)
 
 size_t counter_words(const attn_decode_config *c) { return (size_t)c->max_batch * c->n_kv_heads; }
 
-// The split kernel merges the splits itself when every sequence has at most this many.
 // Compute units of the current device (cached per device, safe across host threads; 0 if
 // the query fails).
 int compute_units()
@@ -495,7 +532,7 @@ int compute_units()
 int chunks_per_split(const attn_decode_config *c)
 {
     if (c->fused_merge_max_splits < 0) return 0;
-    const int lim = c->fused_merge_max_splits == 0 ? kFusedSplits : c->fused_merge_max_splits;
+    const int lim = split_limit(c);
     const int sf = max_splits(c);
     int R = (sf + lim - 1) / lim;
     const long rows = (long)c->n_kv_heads * c->max_batch;  // workgroups per split index
@@ -503,6 +540,23 @@ int chunks_per_split(const attn_decode_config *c)
     if (slots > 0 && (long)sf * rows > 2 * slots)
         while (R < sf && (long)((sf + R - 1) / R) * rows > slots * 3 / 2) ++R;
     return R;
+}
+
+// Splits of the grid: S, and more where the batch has few rows.  A sequence of at most this
+// many chunks takes one per split although S may be fewer, since in a batch of mixed
+// lengths the few long sequences are the longest chain: 24 sequences of the standard mix
+// on 4 heads (S = 8) 18.1 us at R = ceil(chunks / 8), 15.3 with up to 12 splits; where all
+// are that long it is even at 12 chunks (40.5 / 41.0) and loses at 16 (46.7 / 52.8).  Every
+// split is one more workgroup per row that short sequences leave idle, so many rows take
+// fewer, and rows that fill the slots (two workgroups per CU) by themselves none: 96
+// sequences of 512 tokens on 8 heads 42.2 us with one split each, 48.8 with two.
+int grid_splits(const attn_decode_config *c, int S)
+{
+    const long rows = (long)c->n_kv_heads * c->max_batch;
+    if (rows >= kGridWorkgroups / 6) return S;
+    const long per = kGridWorkgroups / rows;
+    const int few = per > 12 ? 12 : (int)per, slots = partial_slots(c);
+    return S > few ? S : (few < slots ? few : slots);
 }
 
 bool aligned(const void *p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
@@ -569,8 +623,9 @@ extern "C" int attn_decode_forward(const attn_decode_config *cfg, void *workspac
     hipStream_t st = (hipStream_t)stream;
     if (R > 0) {
         const int S = (max_splits(cfg) + R - 1) / R;  // at most the limit, and at most partial_slots
+        const int grid_s = grid_splits(cfg, S);
         if (S > partial_slots(cfg)) return fail(ATTN_ERR_INVALID, "internal: %d splits exceed the workspace", S);
-        attn_split_kernel<true><<<dim3(S, Hkv, batch), 256, 0, st>>>(
+        attn_split_kernel<true><<<dim3(Hkv, batch, grid_s), 256, 0, st>>>(
             (const uint16_t *)q, (const uint16_t *)k_cache, (const uint16_t *)v_cache, n_pages, block_table,
             cfg->max_pages_per_seq, ctx_lens, Hkv, G, scale * kLog2e, po, pml, S, R, cnt, (uint16_t *)out);
         const hipError_t e = hipGetLastError();
@@ -578,7 +633,7 @@ extern "C" int attn_decode_forward(const attn_decode_config *cfg, void *workspac
         return ATTN_OK;
     }
     const int S = max_splits(cfg);
-    attn_split_kernel<false><<<dim3(S, Hkv, batch), 256, 0, st>>>(
+    attn_split_kernel<false><<<dim3(Hkv, batch, S), 256, 0, st>>>(
         (const uint16_t *)q, (const uint16_t *)k_cache, (const uint16_t *)v_cache, n_pages, block_table,
         cfg->max_pages_per_seq, ctx_lens, Hkv, G, scale * kLog2e, po, pml, S, 1, cnt, (uint16_t *)out);
     hipError_t e = hipGetLastError();

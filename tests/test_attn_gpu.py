@@ -115,6 +115,32 @@ def test_fused_merge_matches_two_kernels(dev, name):
     assert torch.all(out4[nb:] == 0x7FC1)  # rows past the batch untouched
 
 
+# (query heads, key/value heads, block-table row in pages, lengths): up to 32 splits where the
+# rows are fewer than 16 (one chunk per split, then two); 24 sequences of 4 heads whose row
+# of 16 chunks has 8 splits (one chunk per split up to 12 chunks, two from 13); 128 rows with
+# a grid of 12; 520 rows, which keep the configuration's one split
+SPLIT_RULES = [(4, 1, 640, [8192, 4097, 8193, 10240, 0, 17 * 256]),
+               (16, 4, 256, [3072, 3073, 2049, 4096, 1, 2048] + [100] * 18),
+               (8, 8, 256, [4096, 2817, 3072, 300] + [16] * 12),
+               (8, 8, 48, [768, 257, 256, 5] + [16] * 61)]
+
+
+@pytest.mark.parametrize("hq,hkv,pages,lens", SPLIT_RULES, ids=lambda v: "" if isinstance(v, list) else str(v))
+def test_split_rules(dev, hq, hkv, pages, lens):
+    """Lengths on both sides of every switch of the splits per sequence, against the oracle;
+    a call with the first sequences only repeats their rows bit for bit."""
+    cfg = A.AttnConfig(f"splits-{hq}x{hkv}", hq, hkv, len(lens), "standard")
+    h = A.host_attn(cfg, seed=331 + hq, ctx=np.array(lens, np.int32), max_pages=pages)
+    scale = 1 / np.sqrt(128)
+    out, m, d = run_gpu(cfg, h, dev, scale)
+    ref = oracle.attn_decode(h.q, h.k_cache, h.v_cache, h.block_table, h.ctx, scale)
+    check(bf16_to_f64(out), ref, label=cfg.name)
+    out2 = torch.empty_like(out)
+    m.forward(d["q"], d["k_cache"], d["v_cache"], h.n_pages, d["block_table"], d["ctx"], 3, scale, out2)
+    torch.cuda.synchronize(dev)
+    assert torch.equal(out2[:3], out[:3])
+
+
 def test_block_table_wider_than_contexts(dev):
     """A block-table row longer than any context: more splits than any sequence uses."""
     cfg = A.AttnConfig("wide-table", 16, 2, 5, "standard")
