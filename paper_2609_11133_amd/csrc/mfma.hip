@@ -1539,18 +1539,28 @@ __global__ void pack_scales_kernel(const uint8_t *__restrict__ src, uint8_t *__r
 
 }  // namespace
 
-// Token rows of a step's chunk records (MFMA experts): 128 for FP8 layers once an expert has
-// enough tokens on average for the streams saved to outweigh the wide kernels' item
-// starts, which weigh more the shorter the down projection's rows (I) are.  Packed,
-// step us (32-token chunks / wide): 480B-shaped (I 2560) 6.4 pairs per expert 1,240 /
-// 1,253, 12.8 1,338 / 1,279; 235B-shaped (I 1536) 12 468 / 473, 16 503 / 485, 24 587 /
-// 519; I 1024: 18 119 / 125, 24 142 / 138; I 640: 19 453 / 470, 32 669 / 536; I 384: 32
-// 70 / 85, 80 125 / 119.  Row-major weights: I 1536, 8 512 / 580, 16 600 / 608.
+// Token rows of a step's chunk records (MFMA experts): 128 for FP8 layers (64 for NVFP4, 32
+// for MXFP4) once an expert has enough tokens on average for the weight streams saved to
+// outweigh the wide kernels' item starts, which weigh more the shorter the down
+// projection's rows (I) are.  Step us, 32-token chunks / wide, at pairs per expert:
+//   FP8 packed     I 2560: 6.4 1,240 / 1,253, 12.8 1,338 / 1,279; I 1536: 12 468 / 473, 16
+//                  503 / 485, 24 587 / 519; I 1024: 18 119 / 125, 24 142 / 138; I 640: 19
+//                  453 / 470, 32 669 / 536; I 384: 32 70 / 85, 80 125 / 119
+//   FP8 row-major  I 1536: 8 512 / 580, 16 600 / 608
+//   NVFP4 packed   I 2560: 9.6 805 / 831; I 1536: 11.3 303 / 307, 13.1 313 / 312, 16 331 /
+//                  317, 62 820 / 604; I 1024: 12 86 / 88, 16 95 / 92; I 512: 16 79 / 86, 32
+//                  107 / 101
+//   NVFP4 row-major (whose 32-token kernels read 16 bytes of scales per row)  I 1536: 2
+//                  312 / 314, 4 357 / 334, 62 1,028 / 664; I 1024: 3 93 / 89; I 512: 8 76 /
+//                  81, 16 94 / 94
 int chunk_tokens(const Layer &L, int T, int k)
 {
-    if (L.wfmt != 0 || L.H % (32 * kWideW)) return kMfmaChunk;
-    const long work = (long)T * k * L.I, line = L.wlayout ? 20000 : 26000;
-    return work > line * L.E ? kWideChunk : kMfmaChunk;
+    const long pairs = (long)T * k, E = L.E;
+    if (L.wfmt == 0 && L.H % (32 * kWideW) == 0)
+        return pairs * L.I > (L.wlayout ? 20000 : 26000) * E ? kWideChunk : kMfmaChunk;
+    if (L.wfmt == 2 && L.I % 128 == 0)
+        return pairs > (L.wlayout ? 13 : 3) * E && pairs * L.I > (L.wlayout ? 13000 : 7000) * E ? kWideChunk4 : kMfmaChunk;
+    return kMfmaChunk;
 }
 
 hipError_t launch_w13_mfma(const Layer &L, const void *expert_w, const void *scales, int T, int k,

@@ -56,7 +56,8 @@ struct MetaIdx {
 __host__ __device__ inline int max_mfma_chunks(int E, int Tmax, int kmax) { return E + (Tmax * kmax + 31) / 32; }
 
 constexpr int kMfmaChunk = 32;   // tokens of a chunk record (two 16-column tiles)
-constexpr int kWideChunk = 128;  // tokens of a chunk record of the large-batch kernels
+constexpr int kWideChunk = 128;  // tokens of a chunk record of the large-batch kernels, FP8 weights
+constexpr int kWideChunk4 = 64;  // ... and NVFP4 weights
 // Screened routing by default from T*E*H >= 2^26 multiply-adds of exact logits: below
 // it the fixed costs of the extra pass outweigh the logits it saves.
 constexpr long kScreenMinMacs = 1L << 26;

@@ -45,6 +45,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "moe_internal.h"
 
 namespace moe {
@@ -131,26 +133,27 @@ struct Stager {
     }
 };
 
+// One instruction's bf16 operand: the eight E2M1 codes of w times their block scale s.
+__device__ inline u32x4v dequant_8(uint32_t w, float s)
+{
+    f32x2 v[4];
+    v[0] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 0);
+    v[1] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 1);
+    v[2] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 2);
+    v[3] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 3);
+    u32x4v a;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) a[b] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v[b] * s, bf16x2));
+    return a;
+}
+
 // Four bf16x8 operands (instructions q = 4h..4h+3 of a block) from 16 of a lane's
 // weight bytes (w: inputs [64g + 32h, 64g + 32h + 32)) and their two E4M3 block
 // scales (s0: the first 16 inputs, s1: the next 16).
 __device__ inline void dequant(const u32x4v &w, float s0, float s1, bf16x8 (&a)[4])
 {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const float s = q < 2 ? s0 : s1;
-        f32x2 v[4];
-        v[0] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[q], 1.0f, 0);
-        v[1] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[q], 1.0f, 1);
-        v[2] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[q], 1.0f, 2);
-        v[3] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[q], 1.0f, 3);
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const bf16x2 p = __builtin_convertvector(v[b] * s, bf16x2);
-            a[q][2 * b] = p.x;
-            a[q][2 * b + 1] = p.y;
-        }
-    }
+    for (int q = 0; q < 4; ++q) a[q] = __builtin_bit_cast(bf16x8, dequant_8(w[q], q < 2 ? s0 : s1));
 }
 
 // A raw buffer over memory the whole wave addresses from one base (scalar registers).
@@ -162,28 +165,26 @@ __device__ inline __amdgpu_buffer_rsrc_t uniform_rsrc(const void *p)
     return __builtin_amdgcn_make_buffer_rsrc((void *)(((uint64_t)hi << 32) | lo), (short)0, -1, kRawBufferWord3);
 }
 
-// The f16 form of dequant: E2M1 pairs to f16 (exact), times the block scale, which the
-// E4M3 conversion gave as f16 (s.x: the first 16 inputs, s.y: the next 16), by packed
-// multiplies whose operand selection broadcasts one half of s.  A product of an E2M1
-// value and an E4M3 scale has at most 6 significant bits and lies in [2^-10, 2688] or is
-// zero: exact in f16.
+// The f16 form of dequant_8 and dequant: E2M1 pairs to f16 (exact), times the block scale,
+// which the E4M3 conversion gave as f16 (s.x: the first 16 inputs, s.y: the next 16), by
+// packed multiplies whose operand selection broadcasts one half of s.  A product of an
+// E2M1 value and an E4M3 scale has at most 6 significant bits and lies in [2^-10, 2688] or
+// is zero: exact in f16.
+__device__ inline u32x4v dequant16_8(uint32_t w, _Float16 s)
+{
+    const f16x2 m = {s, s};
+    u32x4v a;
+    a[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 0) * m);
+    a[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 1) * m);
+    a[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 2) * m);
+    a[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 3) * m);
+    return a;
+}
+
 __device__ inline void dequant16(const u32x4v &w, f16x2 s, f16x8 (&a)[4])
 {
-    const f16x2 m0 = {s.x, s.x}, m1 = {s.y, s.y};
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const f16x2 m = q < 2 ? m0 : m1;
-        f16x2 v[4];
-        v[0] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w[q], 1.0f, 0) * m;
-        v[1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w[q], 1.0f, 1) * m;
-        v[2] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w[q], 1.0f, 2) * m;
-        v[3] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w[q], 1.0f, 3) * m;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            a[q][2 * b] = v[b].x;
-            a[q][2 * b + 1] = v[b].y;
-        }
-    }
+    for (int q = 0; q < 4; ++q) a[q] = __builtin_bit_cast(f16x8, dequant16_8(w[q], q < 2 ? s.x : s.y));
 }
 
 // Streams this wave's 16-row weight tile (this lane's row `arow`, its E4M3 scale row
@@ -470,6 +471,411 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(T16 ? 3 
     }
 }
 
+// ------------------------------------------------------------------ wide chunks
+//
+// Large batches: chunks of up to 64 tokens (kWideChunk4), so that an expert's weights are
+// streamed and converted once for most of its tokens.  As for FP8 weights (mfma.hip) one
+// persistent workgroup of eight waves per CU takes items from a device counter (`ticket`,
+// zeroed by the step's routing), drawn one item ahead; a wave streams two 16-row tiles (the
+// gate and up rows of the same 16 rows, so h forms in its registers, or two down tiles)
+// against up to four staged token tiles, and its weight ring runs on into the next item.
+// At 64 tokens a 256-input block costs 2,048 LDS cycles of fragment reads and as many of
+// MFMAs per CU, under the 3,200 its 36 KB of weights and scales take at the HBM rate.
+// Longer chunks do not fit the registers (96 tokens spilled).
+//
+// Measured, us (gate/up and down by the stage events, 32-token chunks -> these): the
+// 235B-shaped layer at T=256 with Zipf-skewed routing 159 -> 143 and 110 -> 94; step at
+// T=500 464 -> 379, at T=1000 820 -> 604 (gate/up 274, down 180: 1.5 weight streams per
+// expert at 4.9 TB/s); row-major weights at T=1000 1,028 -> 664.
+
+constexpr int kWW = 8;           // waves per workgroup
+constexpr int kWGrid = 256;      // persistent workgroups: one per CU
+constexpr int kWSegBytes = kWideChunk4 * 2 * kBlk * 2;  // a staged segment: two blocks of 64 token rows
+constexpr int kWSegBlk = 2;      // blocks per staged segment
+
+// One thread's share of staging a segment.
+template <int NT>
+struct WStager {
+    static constexpr int BLK = kWSegBlk, kRow = BLK * kBlk * 2;
+    static constexpr int kPieces = kRow / 16, kRows = 64 * kWW / kPieces;  // token rows per pass
+    static constexpr int Q = 16 * NT / kRows;
+    static_assert(16 * NT % kRows == 0 && kRows % 8 == 0 && 16 * NT * kRow <= kWSegBytes);
+    uint32_t voff[Q];
+    int so;
+    u32x4v code[Q];
+
+    __device__ void init(const int32_t *rows, int slot0, int mc, int K, int tid)
+    {
+        const int p = tid & (kPieces - 1), t0 = tid / kPieces;
+        so = t0 * kRow + swz(p, t0) * 16;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int t = kRows * q + t0;
+            const uint32_t row = t < mc ? (uint32_t)(rows ? rows[t] : slot0 + t) : 0u;
+            voff[q] = t < mc ? row * (uint32_t)K * 2u + 16u * p : kOutOfRange;
+        }
+    }
+    __device__ void load(__amdgpu_buffer_rsrc_t rs, int sg)
+    {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) code[q] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff[q] + (uint32_t)(sg * kRow), 0, 0);
+    }
+    __device__ void store(uint8_t *seg) const
+    {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) *reinterpret_cast<u32x4v *>(seg + so + q * kRows * kRow) = code[q];
+    }
+};
+
+// A wave's two weight tiles of one item (row-major: this lane's rows) and their scales.
+struct WTiles {
+    const uint8_t *arow[2], *srow[2];
+};
+
+// The weight ring of a wave, carried from one item to the next.
+struct WRing {
+    u32x4v A[4][2][2];
+    uint32_t S[4][2];  // scales of a block (not GS)
+    u32x4v SG[2];      // scales of the current group of four blocks (GS)
+};
+
+template <bool PK, bool GS>
+__device__ inline void w_load(WRing &R, int slot, const WTiles &W, int kb, int lane)
+{
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        if constexpr (PK) {
+            const __amdgpu_buffer_rsrc_t tr = uniform_rsrc(W.arow[a]);
+            R.A[slot][a][0] = __builtin_amdgcn_raw_buffer_load_b128(tr, 16u * lane, kb * 2048, kNonTemporal);
+            R.A[slot][a][1] = __builtin_amdgcn_raw_buffer_load_b128(tr, 16u * lane + 1024u, kb * 2048, kNonTemporal);
+            if constexpr (!GS)
+                R.S[slot][a] = __builtin_amdgcn_raw_buffer_load_b32(uniform_rsrc(W.srow[a]), 4u * lane, kb * 256, 0);
+        } else {
+            const int g = lane >> 4;
+            const uint8_t *p = W.arow[a] + (size_t)kb * (kBlk / 2) + 32 * g;
+            R.A[slot][a][0] = *reinterpret_cast<const u32x4v *>(p);
+            R.A[slot][a][1] = *reinterpret_cast<const u32x4v *>(p + 16);
+            R.S[slot][a] = *reinterpret_cast<const uint32_t *>(W.srow[a] + (size_t)kb * (kBlk / 16) + 4 * g);
+        }
+    }
+}
+
+template <bool GS>
+__device__ inline void w_group(u32x4v (&sg)[2], const WTiles &W, int q, int lane)
+{
+    if constexpr (GS)
+#pragma unroll
+        for (int a = 0; a < 2; ++a) sg[a] = __builtin_amdgcn_raw_buffer_load_b128(uniform_rsrc(W.srow[a]), 16u * lane, q * 1024, 0);
+}
+
+// An item's first three blocks into ring slots 0..2.
+template <bool PK, bool GS>
+__device__ inline void w_fill(WRing &R, const WTiles &W, int KB, int lane)
+{
+    w_group<GS>(R.SG, W, 0, lane);
+#pragma unroll
+    for (int u = 0; u < 3; ++u) w_load<PK, GS>(R, u, W, min(u, KB - 1), lane);
+}
+
+// Streams this wave's two weight tiles W over KB blocks against NT staged token tiles
+// (acc[a][j]: tile a, token tile j).  All waves of the workgroup call it together; it
+// synchronises them once per staged segment.  On entry the ring holds the item's first
+// three blocks, on return those of the next item (tiles N).  On return no wave reads `seg`
+// any more.
+template <int NT, bool PK, bool F16, bool GS>
+__device__ inline void w_stream(f32x4 (&acc)[2][NT], WRing &R, const WTiles &W, const WTiles &N, int KB,
+                                __amdgpu_buffer_rsrc_t rs, WStager<NT> &st, uint8_t *seg, int lane)
+{
+    constexpr int BLK = kWSegBlk, kRow = BLK * kBlk * 2;
+    const int r = lane & 15, g = lane >> 4;
+    const int nseg = (KB + BLK - 1) / BLK;
+    // a block past the end is the next item's block of the same ring slot
+    auto loadA = [&](int slot, int kb) {
+        const bool in = kb < KB;
+        WTiles T;
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            T.arow[a] = in ? W.arow[a] : N.arow[a];
+            T.srow[a] = in ? W.srow[a] : N.srow[a];
+        }
+        w_load<PK, GS>(R, slot, T, in ? kb : slot, lane);
+    };
+    // Piece 32kk + 8g + m (m = 4h + q) of token row r sits at row r's start + 512 kk + 128 g +
+    // 16 (m ^ (r & 7)) (see swz); token tile j adds 16 rows.
+    const int base = r * kRow + 128 * g + 16 * (r & 7);
+    // One instruction's operands at a time (m) for both tiles, and the fragments of two token
+    // tiles while the two before are multiplied: more of either does not fit the registers.
+    constexpr int JG = 2, NG = NT / JG;
+    auto compute = [&](int slot, const uint8_t *S, int kk, const uint32_t (&sw)[2]) {
+        f32x2 s01[2], s23[2];
+        f16x2 h01[2], h23[2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            s01[a] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(sw[a], 1.0f, false);
+            s23[a] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(sw[a], 1.0f, true);
+            h01[a] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(sw[a], 1.0f, false);
+            h23[a] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(sw[a], 1.0f, true);
+        }
+        u32x4v b[2][JG];
+        auto readB = [&](int i) {  // fragment group i = (m, j group)
+            const int m = i / NG, j0 = i % NG * JG;
+#pragma unroll
+            for (int j = 0; j < JG; ++j)
+                b[i & 1][j] = *reinterpret_cast<const u32x4v *>(S + ((base ^ (16 * m)) + 512 * kk + (j0 + j) * 16 * kRow));
+        };
+        readB(0);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const int h = m >> 2, q = m & 3;
+            u32x4v op[2];
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const uint32_t w = R.A[slot][a][h][q];
+                if constexpr (F16)
+                    op[a] = dequant16_8(w, h ? (q < 2 ? h23[a].x : h23[a].y) : (q < 2 ? h01[a].x : h01[a].y));
+                else
+                    op[a] = dequant_8(w, h ? (q < 2 ? s23[a].x : s23[a].y) : (q < 2 ? s01[a].x : s01[a].y));
+            }
+#pragma unroll
+            for (int i = 0; i < NG; ++i) {
+                const int ii = m * NG + i;
+                if (ii + 1 < 8 * NG) readB(ii + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < JG; ++j)
+#pragma unroll
+                    for (int a = 0; a < 2; ++a) {
+                        f32x4 &c = acc[a][i * JG + j];
+                        if constexpr (F16)
+                            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, op[a]),
+                                                                       __builtin_bit_cast(f16x8, b[ii & 1][j]), c, 0, 0, 0);
+                        else
+                            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, op[a]),
+                                                                        __builtin_bit_cast(bf16x8, b[ii & 1][j]), c, 0, 0, 0);
+                    }
+            }
+        }
+    };
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[a][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    st.load(rs, 0);
+    st.store(seg);
+    st.load(rs, min(1, nseg - 1));
+    sync_lds();
+    int kb = 0;
+    for (; kb + 4 <= KB; kb += 4) {  // four blocks per iteration: 4 / BLK segments
+        const int sg = kb / BLK;
+        u32x4v SN[2];
+        w_group<GS>(SN, kb + 8 <= KB ? W : N, kb + 8 <= KB ? kb / 4 + 1 : 0, lane);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            loadA((u + 3) & 3, kb + u + 3);
+            __builtin_amdgcn_sched_barrier(0);
+            const int p = (u / BLK) & 1;  // the block's buffer
+            uint32_t sw[2];
+#pragma unroll
+            for (int a = 0; a < 2; ++a) sw[a] = GS ? R.SG[a][u] : R.S[u][a];
+            compute(u, seg + p * kWSegBytes, u % BLK, sw);
+            if ((u + 1) % BLK == 0) {
+                st.store(seg + (p ^ 1) * kWSegBytes);
+                st.load(rs, min(sg + 2 + u / BLK, nseg - 1));
+                sync_lds();
+            }
+        }
+        if constexpr (GS)
+#pragma unroll
+            for (int a = 0; a < 2; ++a) R.SG[a] = SN[a];
+    }
+    // Fewer than four blocks remain, in ring slots 0..2; their first segment is staged, the
+    // next one sits in the stager's registers.  A slot takes the next item's block once its
+    // own is multiplied (the slots past the remainder took theirs above, or do now).
+    if (kb < KB) {
+        const int sg = kb / BLK, rem = KB - kb;
+        if (KB < 4) {
+            if (rem < 2) w_load<PK, GS>(R, 1, N, min(1, KB - 1), lane);
+            if (rem < 3) w_load<PK, GS>(R, 2, N, min(2, KB - 1), lane);
+        }
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            if (u < rem) {
+                const int p = (u / BLK) & 1;
+                if (u && u % BLK == 0) {
+                    st.store(seg + p * kWSegBytes);
+                    st.load(rs, min(sg + 1 + u / BLK, nseg - 1));
+                    sync_lds();
+                }
+                const uint32_t sw[2] = {R.S[u][0], R.S[u][1]};  // never grouped: KB is no multiple of four
+                compute(u, seg + p * kWSegBytes, u % BLK, sw);
+                w_load<PK, GS>(R, u, N, min(u, KB - 1), lane);
+            }
+        }
+        sync_lds();
+    }
+}
+
+// Calls go(integral_constant NT) with the token tiles of a chunk of mc tokens.
+template <class F>
+__device__ inline void w_tiles_of(int mc, F go)
+{
+    if (mc > 32) go(std::integral_constant<int, 4>{});
+    else go(std::integral_constant<int, 2>{});
+}
+
+// A chunk record, the same for every lane, in scalar registers.
+__device__ inline int4 w_rec(const int4 *recs, int i)
+{
+    const int4 r = recs[i];
+    return make_int4(__builtin_amdgcn_readfirstlane(r.x), __builtin_amdgcn_readfirstlane(r.y),
+                     __builtin_amdgcn_readfirstlane(r.z), 0);
+}
+
+// gate/up: item = (chunk, 16 * kWW rows of the intermediate dimension); wave w streams the
+// gate and the up rows i0 + 16w .. +16.
+template <bool PK, bool GS>
+__global__ __launch_bounds__(64 * kWW) __attribute__((amdgpu_waves_per_eu(2))) void w13_nvfp4_wide_kernel(
+    const uint8_t *__restrict__ ew, const uint8_t *__restrict__ es, const int32_t *__restrict__ meta,
+    const int32_t *__restrict__ tok_of, const _Float16 *__restrict__ x16, const int32_t *__restrict__ xk,
+    __bf16 *__restrict__ hb, int32_t *ticket, int T, int H, int I, int E, size_t ewb, size_t esb)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t seg[2 * kWSegBytes];
+    __shared__ int s_tok[2][kWideChunk4];  // token rows of this item's chunk and the next one's
+    __shared__ int s_next;
+    const MetaIdx mi{E};
+    const int tiles = I / (16 * kWW);
+    const int n_items = meta[mi.n_mfma_chunks()] * tiles;
+    const int4 *recs = reinterpret_cast<const int4 *>(meta + mi.chunk_rec());
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const __amdgpu_buffer_rsrc_t xr = raw_rsrc(x16, (uint32_t)T * (uint32_t)H * 2u);
+    int item = blockIdx.x, nxt = item + gridDim.x;
+    if (item >= n_items) return;  // uniform over the workgroup
+    auto row0 = [&](int it) { return (it % tiles) * (16 * kWW) + 16 * wave; };
+    auto tiles_of = [&](WTiles &W, int e, int r0) {
+        const uint8_t *we = ew + (size_t)e * ewb, *se = es + (size_t)e * esb + 16;
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            const int row = a * I + r0 + (PK ? 0 : r);
+            W.arow[a] = we + (size_t)row * (H / 2);
+            W.srow[a] = se + (size_t)row * (H / 16);
+        }
+    };
+    int4 rec = w_rec(recs, item / tiles);  // {expert, first slot, tokens, -}
+    WTiles W, N;
+    tiles_of(W, rec.x, row0(item));
+    WRing R;
+    w_fill<PK, GS>(R, W, H / kBlk, lane);
+    if (tid < kWideChunk4) s_tok[0][tid] = tid < rec.z ? tok_of[rec.y + tid] : 0;
+    __syncthreads();
+    for (int p = 0;; p ^= 1) {
+        const int after = tid == 0 ? atomicAdd(ticket, 1) + 2 * (int)gridDim.x : 0;
+        const bool more = nxt < n_items;
+        const int ni = more ? nxt : item;  // after the last item: its own blocks again
+        const int4 nrec = w_rec(recs, ni / tiles);
+        const int ntok = tid < nrec.z && tid < kWideChunk4 ? tok_of[nrec.y + tid] : 0;
+        tiles_of(N, nrec.x, row0(ni));
+        w_tiles_of(rec.z, [&](auto nt) {
+            constexpr int NT = decltype(nt)::value;
+            WStager<NT> st;
+            st.init(s_tok[p], 0, rec.z, H, tid);
+            f32x4 acc[2][NT];
+            w_stream<NT, PK, true, GS>(acc, R, W, N, H / kBlk, xr, st, seg, lane);
+            const float *ts = reinterpret_cast<const float *>(es + (size_t)rec.x * esb);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                if (16 * j + r < rec.z) {
+                    // token column 16j + r: undo its 2^-k (2^k is exact: -112 <= k <= 113)
+                    const float p2k = __uint_as_float((uint32_t)(127 + xk[s_tok[p][16 * j + r]]) << 23);
+                    const float tg = ts[0] * p2k, tu = ts[1] * p2k;
+                    bf16x2 hv[2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const float g0 = tg * acc[0][j][2 * i], g1 = tg * acc[0][j][2 * i + 1];
+                        const f32x2 h = {g0 / (1.0f + expf(-g0)) * (tu * acc[1][j][2 * i]),
+                                         g1 / (1.0f + expf(-g1)) * (tu * acc[1][j][2 * i + 1])};
+                        hv[i] = __builtin_convertvector(h, bf16x2);
+                    }
+                    *reinterpret_cast<uint2 *>(hb + ((size_t)rec.y + 16 * j + r) * I + row0(item) + 4 * g) =
+                        make_uint2(__builtin_bit_cast(uint32_t, hv[0]), __builtin_bit_cast(uint32_t, hv[1]));
+                }
+            }
+        });
+        if (!more) return;
+        if (tid < kWideChunk4) s_tok[p ^ 1][tid] = ntok;
+        if (tid == 0) s_next = after;
+        sync_lds();
+        item = nxt;
+        nxt = __builtin_amdgcn_readfirstlane(s_next);
+        rec = nrec;
+        W = N;
+    }
+}
+
+// down: item = (chunk, 32 * kWW output rows); wave w streams rows n0 + 32w .. +32 as two tiles.
+template <bool PK, bool GS>
+__global__ __launch_bounds__(64 * kWW) __attribute__((amdgpu_waves_per_eu(2))) void w2_nvfp4_wide_kernel(
+    const uint8_t *__restrict__ ew, const uint8_t *__restrict__ es, const int32_t *__restrict__ meta,
+    const __bf16 *__restrict__ hb, float *__restrict__ obuf, int32_t *ticket, int P, int H, int I, int E, size_t ewb,
+    size_t esb)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t seg[2 * kWSegBytes];
+    __shared__ int s_next;
+    const MetaIdx mi{E};
+    const int tiles = H / (32 * kWW);
+    const int n_items = meta[mi.n_mfma_chunks()] * tiles;
+    const int4 *recs = reinterpret_cast<const int4 *>(meta + mi.chunk_rec());
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const __amdgpu_buffer_rsrc_t hr = raw_rsrc(hb, (uint32_t)P * (uint32_t)I * 2u);
+    int item = blockIdx.x, nxt = item + gridDim.x;
+    if (item >= n_items) return;  // uniform over the workgroup
+    auto row0 = [&](int it) { return (it % tiles) * (32 * kWW) + 32 * wave; };
+    auto tiles_of = [&](WTiles &W, int e, int r0) {
+        const uint8_t *we = ew + (size_t)e * ewb + (size_t)I * H, *se = es + (size_t)e * esb + 16 + (size_t)2 * I * (H / 16);
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            const int row = r0 + 16 * a + (PK ? 0 : r);
+            W.arow[a] = we + (size_t)row * (I / 2);
+            W.srow[a] = se + (size_t)row * (I / 16);
+        }
+    };
+    int4 rec = w_rec(recs, item / tiles);
+    WTiles W, N;
+    tiles_of(W, rec.x, row0(item));
+    WRing R;
+    w_fill<PK, GS>(R, W, I / kBlk, lane);
+    for (;;) {
+        const int after = tid == 0 ? atomicAdd(ticket, 1) + 2 * (int)gridDim.x : 0;
+        const bool more = nxt < n_items;
+        const int ni = more ? nxt : item;  // after the last item: its own blocks again
+        const int4 nrec = w_rec(recs, ni / tiles);
+        tiles_of(N, nrec.x, row0(ni));
+        w_tiles_of(rec.z, [&](auto nt) {
+            constexpr int NT = decltype(nt)::value;
+            WStager<NT> st;
+            st.init(nullptr, rec.y, rec.z, I, tid);
+            f32x4 acc[2][NT];
+            w_stream<NT, PK, false, GS>(acc, R, W, N, I / kBlk, hr, st, seg, lane);
+            const float td = reinterpret_cast<const float *>(es + (size_t)rec.x * esb)[2];
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                if (16 * j + r < rec.z)
+#pragma unroll
+                    for (int a = 0; a < 2; ++a)
+                        *reinterpret_cast<f32x4 *>(obuf + ((size_t)rec.y + 16 * j + r) * H + row0(item) + 16 * a + 4 * g) =
+                            td * acc[a][j];
+        });
+        if (!more) return;
+        if (tid == 0) s_next = after;
+        sync_lds();
+        item = nxt;
+        nxt = __builtin_amdgcn_readfirstlane(s_next);
+        rec = nrec;
+        W = N;
+    }
+}
+
 constexpr int kWaves = 4;
 
 // Workgroups for `items_per_chunk` items per chunk record (see mfma_grid in mfma.hip).
@@ -549,6 +955,17 @@ hipError_t launch_w13_nvfp4(const Layer &L, const void *expert_w, const void *sc
                             const int32_t *meta, const int32_t *tok_of, const Workspace &ws, hipStream_t st)
 {
     const uint8_t *ew = (const uint8_t *)expert_w, *es = (const uint8_t *)scales;
+    if (chunk_tokens(L, T, k) == kWideChunk4) {
+#define W13W(PK, GS)                                                                                                  \
+    w13_nvfp4_wide_kernel<PK, GS><<<kWGrid, 64 * kWW, 0, st>>>(ew, es, meta, tok_of, ws.x16, ws.xk, (__bf16 *)ws.hb,    \
+                                                               ws.tickets, T, L.H, L.I, L.E, L.expert_w_bytes,       \
+                                                               L.expert_s_bytes)
+        if (grouped_scales(L, L.H)) W13W(true, true);
+        else if (L.wlayout) W13W(true, false);
+        else W13W(false, false);
+#undef W13W
+        return hipGetLastError();
+    }
     if ((long)T * k >= kWideBatchPairs && L.I % (8 * 8) == 0)
         return w13_nvfp4_launch<8, false>(L, ew, es, T, k, meta, tok_of, ws, st);
     if (tile_only(L, T, k)) {
@@ -568,6 +985,17 @@ hipError_t launch_w2_nvfp4(const Layer &L, const void *expert_w, const void *sca
                            const int32_t *meta, const Workspace &ws, hipStream_t st)
 {
     const uint8_t *ew = (const uint8_t *)expert_w, *es = (const uint8_t *)scales;
+    if (chunk_tokens(L, T, k) == kWideChunk4) {
+#define W2W(PK, GS)                                                                                                   \
+    w2_nvfp4_wide_kernel<PK, GS><<<kWGrid, 64 * kWW, 0, st>>>(ew, es, meta, (const __bf16 *)ws.hb, ws.o,                \
+                                                              ws.tickets + 1, T * k, L.H, L.I, L.E, L.expert_w_bytes, \
+                                                              L.expert_s_bytes)
+        if (grouped_scales(L, L.I)) W2W(true, true);
+        else if (L.wlayout) W2W(true, false);
+        else W2W(false, false);
+#undef W2W
+        return hipGetLastError();
+    }
     if (!L.wlayout) {
         dim3 grid(nvfp4_grid(L, T, k, L.H / (16 * kWaves))), block(64 * kWaves);
         w2_nvfp4_kernel<kWaves, false, false, false><<<grid, block, 0, st>>>(

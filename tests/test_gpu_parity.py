@@ -522,6 +522,34 @@ def test_wide_chunks(dev, cfg, layout):
         assert any(lo <= n <= hi for n in sizes), (lo, hi, sorted(sizes))
 
 
+# The large-batch NVFP4 kernels (64-token chunks): K block counts of 5 and 3, 2 and 1, and 8
+# and 4 (grouped packed scales in both projections).
+WIDE_NV = [LayerConfig("nv-wide-k5-3", 1280, 8, 2, 768, "bf16", "bf16", "nvfp4", "zipf:1.1", []),
+           LayerConfig("nv-wide-k2-1", 512, 8, 2, 256, "bf16", "bf16", "nvfp4", "zipf:1.1", []),
+           LayerConfig("nv-wide-k8-4", 2048, 8, 2, 1024, "bf16", "bf16", "nvfp4", "zipf:1.1", [])]
+
+
+@pytest.mark.parametrize("cfg", WIDE_NV, ids=lambda c: c.name)
+@pytest.mark.parametrize("layout", [0, 1], ids=["rows", "packed"])
+def test_nvfp4_wide_chunks(dev, cfg, layout):
+    """NVFP4 layers on both sides of the switch to 64-token chunks (more than 13 pairs and
+    T*k*I above 13,000 per expert packed, 3 and 7,000 row-major); the Zipf-skewed batches
+    give chunks of both token-tile counts and several chunks of one expert."""
+    hl = W.host_layer(cfg, seed=621)
+    per = max(13, 13000 // cfg.inter) if layout else max(3, 7000 // cfg.inter)
+    edge = per * cfg.n_experts // cfg.topk
+    run = Run(cfg, hl, dev, max_tokens=300, weight_layout=layout)
+    sizes = set()
+    for T in (edge, edge + cfg.n_experts, 300):
+        check_layer(run, W.host_x(cfg, T, seed=621 + T), label=f"{cfg.name} T={T}")
+        _, counts = run.m.stats()
+        say(f"[wide] {cfg.name} T={T}: tokens per expert {sorted(counts, reverse=True)}")
+        if T > edge:
+            sizes |= {c % 64 for c in counts} | {64 * (c >= 64) for c in counts}
+    assert max(counts) > 128
+    assert any(1 <= n <= 32 for n in sizes) and any(33 <= n <= 64 for n in sizes)
+
+
 PK_NV_WIDE = LayerConfig("pk-nv-wide", 1024, 16, 8, 1024, "bf16", "bf16", "nvfp4", "zipf:1.1", [])
 
 
