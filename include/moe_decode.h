@@ -124,7 +124,7 @@ typedef struct moe_decode_config {
                                 every measured token count), negative = never */
     int32_t weight_layout;   /* moe_wlayout of expert_w */
     int32_t screen_min_tokens; /* a forward step with at least this many tokens screens the
-                                router logits: bf16 matrix-core sums give every logit a
+                                router logits: matrix-core sums give every logit a
                                 rigorous bracket, and only the experts whose bracket can
                                 reach the top k get the exact logit (the selection is
                                 the same); needs bf16 x and router_w and H a multiple of

@@ -2,7 +2,10 @@
 // token-to-expert grouping.  One decode step of a MoE layer starts here (the decode
 // lane of the paper's Background section; the MoE models of its Experimental Setup).
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <math.h>
+
+#include <type_traits>
 
 #include "fp8split.h"
 #include "moe_internal.h"
@@ -70,15 +73,14 @@ __device__ inline float round_dd_to_f32(double hi, double lo)
     return ((lo > 0.0) == ((double)other > rd)) ? other : r;
 }
 
-// True if every real number within `bound` of v rounds to the same fp32 value r.
+// True if every real number within `bound` of v rounds to the same fp32 value r: rounding
+// is monotonic, so it does if both ends of an interval that contains them do (the slack
+// covers the ends' own fp64 rounding).
 __device__ inline bool certain_f32(double v, double bound, float &r)
 {
-    r = (float)v;
-    double rd = (double)r;
-    double lo_mid = 0.5 * (rd + (double)nextafterf(r, -INFINITY));
-    double hi_mid = 0.5 * (rd + (double)nextafterf(r, INFINITY));
-    double margin = bound + fabs(v) * 0x1p-51;
-    return (v - lo_mid > margin) && (hi_mid - v > margin);
+    const double m = bound + fabs(v) * 0x1p-51;
+    r = (float)(v - m);
+    return r == (float)(v + m);
 }
 
 template <typename T>
@@ -529,13 +531,36 @@ struct RouteArgs {
     _Float16 *x16;                           // f16 copy of x * 2^-k (NULL: none)
     int32_t *xk;                             // [T] the token's k
     int T, E, H, k, epw, bpt, mstar, do_group, max_chunks, chunk;
-    int id_cache;  // the grouping keeps the choices in LDS (sized by the launch)
+    uint32_t rk;  // ceil(2^32 / k): p / k = mulhi(p, rk) for k > 1, since T * k * k < 2^32
+    int prefix, id_cache;  // the grouping keeps prefix counts / the choices in LDS (sized by the launch)
     // screened routing (large T): per K slice ks, partial sums part[ks][t][e] =
     // (sum x*w, sum |x*w|) and the slice's max |x[t,.]|, max |w[e,.]|
     double2 *part;
     float *xmax, *wmax;
     int KS, Tmax;
+    int screened;  // the step counts as screened (statistics)
 };
+
+// The 2-term FP8 split of one group of 32 inputs of token t (see fp8split.h).
+template <typename XT>
+__device__ __attribute__((always_inline)) inline void write_group(const RouteArgs &A, const XT *xr, int t, int g)
+{
+    const int H = A.H;
+    float v[32], res[32];
+    uint32_t qh[8], ql[8];
+    load32_f32<XT>(xr + g * 32, v);
+    const int ch = exp_for_group(amax_of(v));
+    split_hi(v, ch, qh, res);
+    const int cl = exp_for_group(amax_of(res));
+    split_lo(res, cl, ql);
+    const size_t o = (size_t)t * H + g * 32;
+    reinterpret_cast<uint4 *>(A.xs_hi + o)[0] = make_uint4(qh[0], qh[1], qh[2], qh[3]);
+    reinterpret_cast<uint4 *>(A.xs_hi + o)[1] = make_uint4(qh[4], qh[5], qh[6], qh[7]);
+    reinterpret_cast<uint4 *>(A.xs_lo + o)[0] = make_uint4(ql[0], ql[1], ql[2], ql[3]);
+    reinterpret_cast<uint4 *>(A.xs_lo + o)[1] = make_uint4(ql[4], ql[5], ql[6], ql[7]);
+    A.xe_hi[(size_t)t * (H / 32) + g] = (uint8_t)ch;
+    A.xe_lo[(size_t)t * (H / 32) + g] = (uint8_t)cl;
+}
 
 // The 2-term FP8 split of token t's activations (groups of 32 inputs, see fp8split.h),
 // groups first, first + stride, ... written by the calling thread.
@@ -543,63 +568,66 @@ template <typename XT>
 __device__ __attribute__((always_inline)) inline void write_split(const RouteArgs &A, const XT *xr, int t, int first, int stride)
 {
     const int H = A.H, G = H / 32;
-    for (int g = first; g < G; g += stride) {
-        float v[32], res[32];
-        uint32_t qh[8], ql[8];
-        load32_f32<XT>(xr + g * 32, v);
-        const int ch = exp_for_group(amax_of(v));
-        split_hi(v, ch, qh, res);
-        const int cl = exp_for_group(amax_of(res));
-        split_lo(res, cl, ql);
-        const size_t o = (size_t)t * H + g * 32;
-        reinterpret_cast<uint4 *>(A.xs_hi + o)[0] = make_uint4(qh[0], qh[1], qh[2], qh[3]);
-        reinterpret_cast<uint4 *>(A.xs_hi + o)[1] = make_uint4(qh[4], qh[5], qh[6], qh[7]);
-        reinterpret_cast<uint4 *>(A.xs_lo + o)[0] = make_uint4(ql[0], ql[1], ql[2], ql[3]);
-        reinterpret_cast<uint4 *>(A.xs_lo + o)[1] = make_uint4(ql[4], ql[5], ql[6], ql[7]);
-        A.xe_hi[(size_t)t * (H / 32) + g] = (uint8_t)ch;
-        A.xe_lo[(size_t)t * (H / 32) + g] = (uint8_t)cl;
-    }
+    for (int g = first; g < G; g += stride) write_group<XT>(A, xr, t, g);
 }
 
 // The token's bf16 x as f16 scaled by 2^-k, with k such that max|x| * 2^-k lies in
 // [2^14, 2^15) (k = 0 for a zero row; k >= -112): every value at least 2^-31 of the
 // row's maximum converts exactly.  Called by `nw` waves (wave index w), each of which
 // takes the row maximum on its own (no barrier among them) and converts every nw-th
-// group of eight inputs.
-__device__ inline void bf16x8_f32(const uint16_t *p, float (&v)[8])
-{
-    const uint4 u = *reinterpret_cast<const uint4 *>(p);
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        v[2 * i] = __uint_as_float(w[i] << 16);
-        v[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
-    }
-}
-
+// chunk of 512 inputs.
 __device__ __attribute__((always_inline)) inline void write_x16(const RouteArgs &A, const uint16_t *xr, int t, int w,
                                                                 int nw, int lane)
 {
+    // eight chunks of 512 inputs in flight at a time; a row of one batch converts from registers
+    constexpr int U = 8;
     const int H = A.H;
     float m = 0.f;
-    for (int h = lane * 8; h < H; h += 512) {
-        float v[8];
-        bf16x8_f32(xr + h, v);
+    uint4 c[U];
+    auto load = [&](int h0) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(v[i]));
+        for (int u = 0; u < U; ++u) {
+            const int h = h0 + 512 * u + lane * 8;
+            c[u] = h < H ? *reinterpret_cast<const uint4 *>(xr + h) : make_uint4(0u, 0u, 0u, 0u);
+        }
+    };
+    auto value = [&](int u, float (&v)[8]) {
+        const uint32_t wd[4] = {c[u].x, c[u].y, c[u].z, c[u].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[2 * i] = __uint_as_float(wd[i] << 16);
+            v[2 * i + 1] = __uint_as_float(wd[i] & 0xFFFF0000u);
+        }
+    };
+    for (int h0 = 0; h0 < H; h0 += 512 * U) {
+        load(h0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float v[8];
+            value(u, v);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(v[i]));
+        }
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
     const int ex = m > 0.f ? (int)((__float_as_uint(m) >> 23) & 0xFF) - 127 : 14;  // floor(log2 m) for normal m
     const int kk = max(ex - 14, -112);
     const float sc = __uint_as_float((uint32_t)(127 - kk) << 23);  // 2^-k
-    for (int h = (w * 64 + lane) * 8; h < H; h += nw * 512) {
-        float v[8];
-        bf16x8_f32(xr + h, v);
-        _Float16 q[8];
+    for (int h0 = 0; h0 < H; h0 += 512 * U) {
+        if (H > 512 * U) load(h0);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) q[i] = (_Float16)(v[i] * sc);
-        *reinterpret_cast<uint4 *>(A.x16 + (size_t)t * H + h) = __builtin_bit_cast(uint4, q);
+        for (int u = 0; u < U; ++u) {
+            const int h = h0 + 512 * u + lane * 8;
+            if (u % nw == w && h < H) {
+                float v[8];
+                value(u, v);
+                _Float16 q[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) q[i] = (_Float16)(v[i] * sc);
+                *reinterpret_cast<uint4 *>(A.x16 + (size_t)t * H + h) = __builtin_bit_cast(uint4, q);
+            }
+        }
     }
     if (w == 0 && lane == 0) A.xk[t] = kk;
 }
@@ -617,17 +645,20 @@ __device__ __attribute__((always_inline)) inline void group_pairs(const RouteArg
     const int W = (T + 31) / 32;
     uint32_t *mask = lds;                        // [E][W]
     int32_t *offs = (int32_t *)(lds + E * W);    // [E]
-    int32_t *idc = offs + E;                     // [P] when the launch sized LDS for it: the choices, read once
+    uint16_t *pre = (uint16_t *)(offs + E);      // [E][W] when the launch sized LDS for it: the expert's tokens in earlier words
+    uint16_t *idc = pre + (A.prefix ? E * W : 0);  // [P] when the launch sized LDS for it: the choices, read once
     const bool cached = A.id_cache != 0;
     const MetaIdx mi{E, A.max_chunks};
     int nfb_total = 0, n_exact = A.T * E;
     if (threadIdx.x == 0) {  // in flight during the grouping; each counter is reset by its reader
         nfb_total = atomicExch(A.fb_acc, 0);
-        if (A.KS) n_exact = atomicExch(A.fb_acc + kCandCounterOff, 0);
+        if (A.screened) n_exact = atomicExch(A.fb_acc + kCandCounterOff, 0);
     }
     for (int i = threadIdx.x; i < E * W; i += blockDim.x) mask[i] = 0u;
     __syncthreads();
-    // this thread's choices, eight loads in flight at a time
+    // this thread's choices, eight loads in flight at a time (small loops: at small batches
+    // this code is fetched cold, and 32 unrolled steps took 1.5 us longer)
+    auto token = [&](int p) { return k == 1 ? p : (int)__umulhi((uint32_t)p, A.rk); };  // p / k
     for (int p0 = threadIdx.x; p0 < P; p0 += 8 * blockDim.x) {
         int e8[8];
 #pragma unroll
@@ -639,9 +670,9 @@ __device__ __attribute__((always_inline)) inline void group_pairs(const RouteArg
         for (int u = 0; u < 8; ++u) {
             const int p = p0 + u * blockDim.x;
             if (p < P) {
-                const int tt = p / k;
+                const int tt = token(p);
                 atomicOr(&mask[e8[u] * W + tt / 32], 1u << (tt % 32));
-                if (cached) idc[p] = e8[u];
+                if (cached) idc[p] = (uint16_t)e8[u];
             }
         }
     }
@@ -655,7 +686,10 @@ __device__ __attribute__((always_inline)) inline void group_pairs(const RouteArg
         const int e = eb + j;
         if (e < E) {
             int c = 0;
-            for (int w = 0; w < W; ++w) c += __popc(mask[e * W + w]);
+            for (int w = 0; w < W; ++w) {
+                if (A.prefix) pre[e * W + w] = (uint16_t)c;
+                c += __popc(mask[e * W + w]);
+            }
             cnt[j] = c;
             v[0] += c;
             if (c > 0) {
@@ -698,15 +732,18 @@ __device__ __attribute__((always_inline)) inline void group_pairs(const RouteArg
         A.meta[mi.n_fallback()] = nfb_total;
         A.meta[mi.n_mfma_chunks()] = tot[3];
         A.meta[mi.n_exact()] = n_exact;
-        A.meta[mi.screened()] = A.KS ? 1 : 0;
+        A.meta[mi.screened()] = A.screened;
         st_dev(A.cnt_all, 0);
-        A.fb_acc[kTicketOff] = A.fb_acc[kTicketOff + 1] = 0;
+        if (A.chunk != kMfmaChunk) A.fb_acc[kTicketOff] = A.fb_acc[kTicketOff + 1] = 0;
     }
     __syncthreads();
     for (int p = threadIdx.x; p < P; p += blockDim.x) {
-        const int tt = p / k, e = cached ? idc[p] : ld_dev(&A.ids[p]);
+        const int tt = token(p), e = cached ? idc[p] : ld_dev(&A.ids[p]);
         int rank = __popc(mask[e * W + tt / 32] & ((1u << (tt % 32)) - 1u));
-        for (int w = 0; w < tt / 32; ++w) rank += __popc(mask[e * W + w]);
+        if (A.prefix)
+            rank += pre[e * W + tt / 32];
+        else
+            for (int w = 0; w < tt / 32; ++w) rank += __popc(mask[e * W + w]);
         const int slot = offs[e] + rank;
         A.slot_of[p] = slot;
         A.tok_of[slot] = tt;
@@ -1040,6 +1077,325 @@ __global__ __launch_bounds__(256) void route_cand_kernel(RouteArgs A)
     group_pairs(A, lds, s_scan);
 }
 
+// ------------------------------------------------------------------ tiled routing
+//
+// From a few tokens on, the logits come from fp64 matrix-core sums: workgroup (ks, y, z)
+// forms the 16 x 16 products of experts 16y.. and tokens 16z.. over slice ks of the inputs
+// (v_mfma_f64_16x16x4: products of bf16 or fp32 operands are exact in fp64), so each
+// operand is converted once for sixteen products; converting and adding every product on
+// the vector ALU bounded the logits of route_kernel, and the screen's two launches and
+// dependent phases the large steps.  Each slice's sum goes out with a bound on its sum of
+// |x*w| (the norms' product, by Cauchy-Schwarz).  The last workgroup of a token tile to
+// arrive (a device-scope counter) finishes it while the others write its activation split:
+// it adds the slices, certifies every fp32 rounding as route_kernel does, and runs the
+// top-k softmax of the sixteen tokens, a token per 16-lane row, four to a wave.  The last
+// token tile groups the pairs.
+//
+// Measured by device timestamps, us from the workgroup's start (480B-shaped T=64; 235B-shaped
+// T=256): sums 6.8, 7.2; handed over 9.2, 9.7; certified 13.4, 12.3; top k 15.7, 14.2; written
+// 16.8, 15.5; grouped 21, 25.  Step us, before / now: 235B-shaped NVFP4 T=127 282 / 274;
+// screened, T=256 320 / 313, 480B-shaped T=1000 1,854 / 1,768 (routing 160 / 62).
+
+constexpr int kTileE = 256;  // experts at most (16 keys per lane)
+constexpr int kTileK = 16;   // choices at most (one per lane of a row)
+constexpr int kTileAcc = 4;  // accumulators per wave
+// Below, the fixed phases (the slices' hand-off, a token tile's top-k in one workgroup) cost
+// more than the logits save.  Step us, route_kernel / tiled: 235B-shaped T=24 (3,072 pairs)
+// 208 / 211, T=48 246 / 244, T=64 258 / 257; 480B-shaped T=64 956 / 951; 160 experts T=40
+// (6,400) 281 / 280, T=64 324 / 320; 32 experts T=64 26.9 / 30.3.
+constexpr long kTilePairs = 6400;
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// This wave's LDS stores are done, and later reads are reads: lanes of one wave exchange
+// values through LDS without a workgroup barrier.
+__device__ inline void sync_wave() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// Maximum / minimum over each 16-lane row, the same in all its lanes.
+__device__ inline float row_max(float v)
+{
+    const auto d = [](float x, auto c) {
+        return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), decltype(c)::value, 0xF, 0xF, false));
+    };
+    v = fmaxf(v, d(v, std::integral_constant<int, 0xB1>{}));   // quad_perm [1,0,3,2]
+    v = fmaxf(v, d(v, std::integral_constant<int, 0x4E>{}));   // quad_perm [2,3,0,1]
+    v = fmaxf(v, d(v, std::integral_constant<int, 0x141>{}));  // row_half_mirror
+    return fmaxf(v, d(v, std::integral_constant<int, 0x140>{}));  // row_mirror
+}
+__device__ inline int row_min(int v)
+{
+    v = min(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false));
+    v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false));
+    v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false));
+    return min(v, __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false));
+}
+
+// The k largest logits of the token of each 16-lane row, ties to the lower expert: lane
+// j < k of the row gets choice j (its logit and expert), every lane the last choice's logit
+// and the number of unchosen experts tied with it.
+template <int V>
+__device__ __attribute__((always_inline)) inline void tile_topk(const float *l, int E, int k, int j, float &lj, int &ej,
+                                                                float &last, int &tied)
+{
+    float val[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) val[v] = 16 * v + j < E ? l[16 * v + j] : -INFINITY;
+    lj = 0.f, ej = 0, last = 0.f;
+    for (int c = 0; c < k; ++c) {
+        float m = val[0];
+#pragma unroll
+        for (int v = 1; v < V; ++v) m = fmaxf(m, val[v]);
+        m = row_max(m);
+        int e = INT_MAX;
+#pragma unroll
+        for (int v = V - 1; v >= 0; --v) e = val[v] == m ? 16 * v + j : e;
+        e = row_min(e);
+        if (j == c) lj = m, ej = e;
+#pragma unroll
+        for (int v = 0; v < V; ++v) val[v] = 16 * v + j == e ? -INFINITY : val[v];
+        last = m;
+    }
+    tied = 0;
+#pragma unroll
+    for (int v = 0; v < V; ++v) tied += val[v] == last ? 1 : 0;
+}
+
+__device__ __attribute__((always_inline)) inline void tile_topk_any(const float *l, int E, int k, int j, float &lj, int &ej,
+                                                                    float &last, int &tied)
+{
+    if (E <= 64)
+        tile_topk<4>(l, E, k, j, lj, ej, last, tied);
+    else if (E <= 128)
+        tile_topk<8>(l, E, k, j, lj, ej, last, tied);
+    else if (E <= 192)
+        tile_topk<12>(l, E, k, j, lj, ej, last, tied);
+    else
+        tile_topk<16>(l, E, k, j, lj, ej, last, tied);
+}
+
+// The slices' sums of token t against experts r, r + 16, ...: done(e, sum, bound).  Up to 32
+// 16-byte loads are in flight at a time, past the per-XCD L2 (the producers' stores went
+// past theirs); one expert's at a time cost a memory round trip each.
+template <int KS, class F>
+__device__ __attribute__((always_inline)) inline void tile_sums(const RouteArgs &A, int t, int r, F done)
+{
+    constexpr int VG = KS == 1 ? 16 : 32 / KS, kDeviceScope = 16;  // experts per round; cache policy bit sc1
+    const int E = A.E;
+    const __amdgpu_buffer_rsrc_t pr = screen_rsrc(A.part, (uint32_t)KS * A.Tmax * E * 16u);
+    for (int e0 = r; e0 < E; e0 += 16 * VG) {
+        u32x4v u[VG][KS];
+#pragma unroll
+        for (int v = 0; v < VG; ++v)
+#pragma unroll
+            for (int q = 0; q < KS; ++q)
+                u[v][q] = __builtin_amdgcn_raw_buffer_load_b128(
+                    pr, t < A.T && e0 + 16 * v < E ? (((uint32_t)q * A.Tmax + t) * E + e0 + 16 * v) * 16u : kScreenOOR, 0,
+                    kDeviceScope);
+#pragma unroll
+        for (int v = 0; v < VG; ++v)
+            if (t < A.T && e0 + 16 * v < E) {
+                double S = 0.0, B = 0.0;
+#pragma unroll
+                for (int q = 0; q < KS; ++q) {
+                    S += __longlong_as_double((long long)(((uint64_t)u[v][q][1] << 32) | u[v][q][0]));
+                    B += __longlong_as_double((long long)(((uint64_t)u[v][q][3] << 32) | u[v][q][2]));
+                }
+                done(e0 + 16 * v, S, B);
+            }
+    }
+}
+
+template <typename XT, typename WT>
+__global__ __launch_bounds__(256) void route_tile_kernel(RouteArgs A)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    __shared__ double s_red[4][256];  // the waves' sums; then the list of uncertain logits (16 bits each)
+    __shared__ double s_nx[4][16], s_nw[4][16];
+    __shared__ int s_flag, s_nfb[4];
+    __shared__ int s_scan[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int T = A.T, E = A.E, H = A.H, KS = A.KS;
+    const int ks = blockIdx.x, e0 = blockIdx.y * 16, t0 = blockIdx.z * 16;
+    constexpr uint32_t kX = sizeof(XT), kW = sizeof(WT);
+
+    // 1. this wave's inputs: steps of 32, lane (r, g) the eight from 8g of row r
+    const int nst = H / 32, per = (nst + 4 * KS - 1) / (4 * KS);
+    const int s0 = min(nst, (ks * 4 + wave) * per), s1 = min(nst, s0 + per);
+    const __amdgpu_buffer_rsrc_t xr = screen_rsrc(A.x, (uint32_t)T * H * kX), wr = screen_rsrc(A.wr, (uint32_t)E * H * kW);
+    const uint32_t xo = t0 + r < T ? ((uint32_t)(t0 + r) * H + 8u * g) * kX : kScreenOOR;
+    const uint32_t wo = e0 + r < E ? ((uint32_t)(e0 + r) * H + 8u * g) * kW : kScreenOOR;
+    constexpr int B = kX == 2 && kW == 2 ? 4 : 2;  // steps loaded together
+    Chunk8<XT> xc[2][B];
+    Chunk8<WT> wc[2][B];
+    auto load = [&](int b, int s) {
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            const bool in = s + i < s1;  // past the slice: zeros
+#pragma unroll
+            for (int q = 0; q < (int)(kX / 2); ++q) {
+                const u32x4v u = __builtin_amdgcn_raw_buffer_load_b128(xr, in ? xo + (uint32_t)(s + i) * 32u * kX + 16u * q : kScreenOOR, 0, 0);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) xc[b][i].d[4 * q + c] = u[c];
+            }
+#pragma unroll
+            for (int q = 0; q < (int)(kW / 2); ++q) {
+                const u32x4v u = __builtin_amdgcn_raw_buffer_load_b128(wr, in ? wo + (uint32_t)(s + i) * 32u * kW + 16u * q : kScreenOOR, 0, 0);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) wc[b][i].d[4 * q + c] = u[c];
+            }
+        }
+    };
+    f64x4 acc[kTileAcc];
+#pragma unroll
+    for (int i = 0; i < kTileAcc; ++i) acc[i] = (f64x4){0.0, 0.0, 0.0, 0.0};
+    double nx = 0.0, nw = 0.0;
+    auto compute = [&](int b) {
+#pragma unroll
+        for (int i = 0; i < B; ++i)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const double xv = elem<XT>(xc[b][i], q), wv = elem<WT>(wc[b][i], q);
+                nx = fma(xv, xv, nx);
+                nw = fma(wv, wv, nw);
+                acc[q % kTileAcc] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv, xv, acc[q % kTileAcc], 0, 0, 0);
+            }
+    };
+    load(0, s0);
+    for (int s = s0; s < s1; s += 2 * B) {
+        load(1, s + B);
+        compute(0);
+        load(0, s + 2 * B);
+        compute(1);
+    }
+    // 2. the workgroup's sums.  Lane l holds experts 4i + l/16 (i < 4) of token l%16.
+    nx += __shfl_xor(nx, 16);
+    nx += __shfl_xor(nx, 32);
+    nw += __shfl_xor(nw, 16);
+    nw += __shfl_xor(nw, 32);
+    if (g == 0) {
+        s_nx[wave][r] = nx;
+        s_nw[wave][r] = nw;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s_red[wave][64 * i + lane] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+    __syncthreads();
+    const XT *x = (const XT *)A.x;
+    {
+        const int e = 4 * wave + g, t = r;
+        const double S = (s_red[0][tid] + s_red[1][tid]) + (s_red[2][tid] + s_red[3][tid]);
+        const double x2 = (s_nx[0][t] + s_nx[1][t]) + (s_nx[2][t] + s_nx[3][t]);
+        const double w2 = (s_nw[0][e] + s_nw[1][e]) + (s_nw[2][e] + s_nw[3][e]);
+        if (t0 + t < T && e0 + e < E) {
+            double *p = (double *)(A.part + ((size_t)ks * A.Tmax + t0 + t) * E + e0 + e);
+            st_dev(p, S);
+            st_dev(p + 1, sqrt(x2) * sqrt(w2) * (1.0 + 0x1p-30));
+        }
+    }
+    wait_stores();
+    __syncthreads();
+    const int nwg = gridDim.x * gridDim.y;
+    if (tid == 0) s_flag = atomicAdd(&A.cnt_tok[blockIdx.z * kCounterStride], 1);
+    __syncthreads();
+    const int wg = s_flag;  // order of arrival in the token tile
+    if (wg < nwg - 1 || nwg == 1) {
+        // the others share the token tile's activation split (MFMA path)
+        const int n = nwg > 1 ? nwg - 1 : 1;
+        if (A.xs_hi) {
+            const int G = H / 32;
+            for (int i = wg * 256 + tid; i < 16 * G; i += n * 256) {
+                const int t = t0 + i / G;
+                if (t < T) write_group<XT>(A, x + (size_t)t * H, t, i % G);
+            }
+        } else if constexpr (sizeof(XT) == 2) {
+            if (A.x16)
+                for (int i = wg * 4 + wave; i < 32; i += n * 4)  // two waves per token
+                    if (t0 + i / 2 < T) write_x16(A, x + (size_t)(t0 + i / 2) * H, t0 + i / 2, i & 1, 2, lane);
+        }
+        if (wg < nwg - 1) return;
+    }
+
+    // 3. last workgroup of the token tile, a token per 16-lane row, four to a wave: logits,
+    // top k.  A logit that the bound does not certify matters only if it can reach the
+    // top k: those are recomputed exactly (every one where the logits are asked for) and the
+    // top k taken again, all within the wave.
+    const int tk = 4 * wave + g, t = t0 + tk;
+    float *l = (float *)lds + (size_t)tk * E;  // this row's logits
+    uint16_t *fb = (uint16_t *)&s_red[wave][0];  // the wave's uncertain logits
+    if (lane == 0) s_nfb[wave] = 0;
+    if (tid == 0) st_dev(&A.cnt_tok[blockIdx.z * kCounterStride], 0);
+    {
+        // one accumulator's roundings (its MFMAs, four products each), the accumulators', the
+        // waves' and the slices' additions and the bias; twice the recursive-summation bound
+        const int D = 4 * ((per + 2 * B) * 8 / kTileAcc) + 4 + 4 + KS + 1 + 2;
+        const double gamma = (double)D * 0x1p-52;
+        auto done = [&](int e, double S, double Bd) {
+            const double bias = A.bias ? (double)A.bias[e] : 0.0;
+            float c;
+            if (!certain_f32(S + bias, gamma * (Bd + fabs(bias)), c)) fb[atomicAdd(&s_nfb[wave], 1)] = (uint16_t)(g * kTileE + e);
+            l[e] = c + 0.0f;  // -0 -> +0
+        };
+        if (KS == 1)
+            tile_sums<1>(A, t, r, done);
+        else if (KS == 2)
+            tile_sums<2>(A, t, r, done);
+        else
+            tile_sums<4>(A, t, r, done);
+    }
+    sync_wave();
+    float lj, last;
+    int ej, tied;
+    for (int pass = 0;; ++pass) {
+        tile_topk_any(l, E, A.k, r, lj, ej, last, tied);
+        if (pass) break;
+        const int nfb = __builtin_amdgcn_readfirstlane(s_nfb[wave]);
+        int nex = 0;
+        for (int i = 0; i < nfb; ++i) {
+            const int fg = __builtin_amdgcn_readfirstlane((int)fb[i] / kTileE);
+            const int e = __builtin_amdgcn_readfirstlane((int)fb[i] % kTileE);
+            float *lf = (float *)lds + (size_t)(4 * wave + fg) * E + e;
+            // the canonical logit is the value here or a neighbour of it
+            const float up = nextafterf(nextafterf(*lf, INFINITY), INFINITY);
+            if (A.do_group && up < __shfl(last, 16 * fg)) continue;
+            const float c = wave_logit_exact<XT, WT>(x + (size_t)(t0 + 4 * wave + fg) * H, (const WT *)A.wr + (size_t)e * H,
+                                                     A.bias ? (double)A.bias[e] : 0.0, H, lane);
+            if (lane == 0) *lf = c + 0.0f;
+            ++nex;
+        }
+        if (!nex) break;
+        if (lane == 0) atomicAdd(A.fb_acc, nex);
+        sync_wave();
+    }
+    if (!A.do_group && t < T)
+        for (int e = r; e < E; e += 16) A.logits[(size_t)t * E + e] = l[e];
+    const float p = r < A.k ? expf(lj - __shfl(lj, lane & 48)) : 0.f;
+    float den = p;
+#pragma unroll
+    for (int o = 8; o >= 1; o >>= 1) den += __shfl_xor(den, o);
+    if (t < T && r < A.k) {
+        const size_t o = (size_t)t * A.k + r;
+        const float w = p / den;
+        st_dev(&A.ids[o], ej);
+        A.wts[o] = w;
+        if (A.ids_user) A.ids_user[o] = ej;
+        if (A.wts_user) A.wts_user[o] = w;
+    }
+    if (A.screened) {  // the experts that reach the top k: the choices and those tied with the last
+#pragma unroll
+        for (int o = 8; o >= 1; o >>= 1) tied += __shfl_xor(tied, o);
+        if (r == 0 && t < T) atomicAdd(A.fb_acc + kCandCounterOff, A.k + tied);
+    }
+    if (!A.do_group) return;
+    wait_stores();
+    __syncthreads();
+    if (gridDim.z > 1) {
+        if (tid == 0) s_flag = atomicAdd(A.cnt_all, 1) == (int)gridDim.z - 1;
+        __syncthreads();
+        if (!s_flag) return;
+    }
+    group_pairs(A, lds, s_scan);
+}
+
 __global__ void zero_kernel(int32_t *p, int n)
 {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
@@ -1098,12 +1454,42 @@ hipError_t launch_route(const Layer &L, const RouteParams &P, hipStream_t st)
     A.wmax = P.wmax;
     A.Tmax = P.Tmax;
     A.KS = 0;
+    A.screened = 0;
+    A.rk = (uint32_t)((0x100000000ull + P.k - 1) / P.k);
     const int W = (P.T + 31) / 32;
-    // grouping LDS: bitmasks [E][W] and offsets [E], plus the choices [T*k] while the
-    // whole stays within 64 KiB
-    const size_t base_words = (size_t)L.E * W + L.E, pairs = (size_t)P.T * P.k;
-    A.id_cache = P.do_group && (base_words + pairs) * sizeof(uint32_t) <= 65536 ? 1 : 0;
-    const size_t lds = P.do_group ? sizeof(uint32_t) * (base_words + (A.id_cache ? pairs : 0)) : 0;
+    // grouping LDS: bitmasks [E][W] and offsets [E], then, in 16 bits, prefix counts [E][W]
+    // and the choices [T*k], each while the whole stays within 48 KiB (64 KiB with the
+    // kernels' static arrays)
+    const size_t masks = (size_t)L.E * W, pairs = (size_t)P.T * P.k;
+    size_t lds = sizeof(uint32_t) * (masks + L.E);
+    A.prefix = W > 1 && lds + 2 * masks <= 49152 ? 1 : 0;
+    if (A.prefix) lds += 2 * masks;
+    A.id_cache = lds + 2 * pairs <= 49152 ? 1 : 0;
+    if (A.id_cache) lds += 2 * pairs;
+    if (!P.do_group) lds = 0;
+    // Tiled routing above kTilePairs (token, expert) pairs, and for every screened step it
+    // can take: up to 256 experts, 16 choices.  Four slices of the inputs while the tiles are
+    // at most one per CU, fewer above (235B-shaped NVFP4 layer, step us with 1 / 2 / 4 / 8
+    // slices: T=64 264 / 259 / 257 / 258, T=256 318 / 313 / 311 / 322; 480B-shaped T=1000
+    // 1,768 / 1,767 / 1,783 / 1,804).
+    if ((long)P.T * L.E > kTilePairs && L.E <= kTileE && P.k <= kTileK && P.ks_max > 0) {
+        const int tt = (P.T + 15) / 16, et = (L.E + 15) / 16;
+        int ks = tt * et <= 256 ? 4 : (tt * et <= 512 ? 2 : 1);
+        while (ks > 1 && (ks > P.ks_max || ks > L.H / 256)) ks /= 2;
+        A.KS = ks;
+        A.screened = P.do_group && P.screen && L.act_bf16 && L.router_bf16 ? 1 : 0;
+        const size_t lf = (size_t)16 * L.E * sizeof(float), bytes = lds > lf ? lds : lf;
+        dim3 grid(ks, et, tt), block(256);
+        if (L.act_bf16 && L.router_bf16)
+            route_tile_kernel<uint16_t, uint16_t><<<grid, block, bytes, st>>>(A);
+        else if (L.act_bf16)
+            route_tile_kernel<uint16_t, float><<<grid, block, bytes, st>>>(A);
+        else if (L.router_bf16)
+            route_tile_kernel<float, uint16_t><<<grid, block, bytes, st>>>(A);
+        else
+            route_tile_kernel<float, float><<<grid, block, bytes, st>>>(A);
+        return hipGetLastError();
+    }
     // screened routing: bf16 activations and router, H a multiple of 256, enough work
     if (P.do_group && P.screen && L.act_bf16 && L.router_bf16 && P.ks_max > 0 && L.E <= kMaxE) {
         const int tiles = (P.T + 15) / 16, groups = (L.E + 63) / 64;
@@ -1111,11 +1497,9 @@ hipError_t launch_route(const Layer &L, const RouteParams &P, hipStream_t st)
         int ks = (2048 + waves - 1) / waves;  // about two waves per SIMD
         ks = ks < 1 ? 1 : (ks > P.ks_max ? P.ks_max : ks);
         A.KS = ks;
-        // route_cand_kernel's static arrays take about 12.3 KiB: keep the total within 64 KiB
-        A.id_cache = (base_words + pairs) * sizeof(uint32_t) + kCandStaticLds <= 65536 ? 1 : 0;
-        const size_t lds_c = sizeof(uint32_t) * (base_words + (A.id_cache ? pairs : 0));
+        A.screened = 1;
         screen_kernel<<<dim3(tiles, groups, ks), 256, 0, st>>>(A);
-        route_cand_kernel<<<dim3(P.T), 256, lds_c, st>>>(A);
+        route_cand_kernel<<<dim3(P.T), 256, lds, st>>>(A);
         return hipGetLastError();
     }
     dim3 grid(P.T * bpt), block(256);

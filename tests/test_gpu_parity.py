@@ -300,6 +300,58 @@ def test_exact_fallback_path(dev):
     assert st.n_fallback >= 4
 
 
+# (experts, top-k, hidden, activations, router, tokens): the tiled routing takes over above
+# 6,400 (token, expert) pairs, up to 256 experts and 16 choices; token and expert tiles of
+# 16 with remainders, 4 to 16 keys per lane, 1 to 4 slices of the inputs
+TILED = [(256, 16, 256, "bf16", "bf16", 26), (130, 3, 512, "bf16", "f32", 50), (160, 8, 1280, "f32", "bf16", 41),
+         (64, 1, 2048, "f32", "f32", 101), (65, 5, 768, "bf16", "bf16", 99), (16, 16, 512, "bf16", "bf16", 417),
+         (200, 16, 1024, "bf16", "bf16", 33), (257, 2, 256, "bf16", "bf16", 26), (160, 17, 256, "bf16", "bf16", 41)]
+
+
+@pytest.mark.parametrize("E,k,H,act,router,T", TILED, ids=lambda v: str(v))
+def test_tiled_routing(dev, E, k, H, act, router, T):
+    """Bit-exact logits and selections on both sides of the switch to the tiled routing (and
+    of its limits on experts and choices), with and without grouping, exact and screened."""
+    cfg = LayerConfig(f"tiled-{E}-{k}-{H}", H, E, k, 256, act, router, "fp8", "normal:0.5", [])
+    hl = W.host_layer(cfg, seed=517)
+    for screen in (-1, 1):
+        run = Run(cfg, hl, dev, max_tokens=T, screen_min_tokens=screen)
+        for t in {T, 6400 // E}:
+            x = W.host_x(cfg, t, seed=517 + t)
+            check_layer(run, x, label=f"{cfg.name} T={t} screen={screen}")
+            st, _ = run.m.stats()
+            screened = screen > 0 and act == "bf16" and router == "bf16"
+            assert st.route_screened == screened
+            assert st.n_exact_logits < t * E if screened and k < E else st.n_exact_logits == t * E
+            if screen < 0:
+                check_routing(run, x, label=f"{cfg.name} T={t}")
+
+
+@pytest.mark.parametrize("screen", [-1, 1], ids=["exact", "screened"])
+def test_tiled_routing_degenerate(dev, screen):
+    """The tiled routing on zero rows, ties (to the lower index) and logits on fp32 rounding
+    midpoints, which no error bound certifies."""
+    cfg = LayerConfig("tiled-midpoint", 512, 16, 4, 256, "bf16", "bf16", "fp8", None, [])
+    hl = W.host_layer(cfg, seed=518)
+    one, tiny24, tiny80 = 0x3F80, 0x3380, 0x1780  # 1.0, 2^-24, 2^-80 in bf16
+    hl.router_w[:] = 0
+    hl.router_w[:, 0] = one
+    hl.router_w[5, 1] = tiny24  # l = 1 + 2^-24: tie -> 1.0
+    hl.router_w[6, 1] = tiny24  # l = 1 + 2^-24 + 2^-80: above the tie -> 1 + 2^-23
+    hl.router_w[6, 2] = tiny80
+    T = 405
+    x = np.zeros((T, cfg.hidden), np.uint16)
+    x[:, 0] = x[:, 1] = x[:, 2] = one
+    x[7] = 0
+    x[400:] = 0
+    run = Run(cfg, hl, dev, max_tokens=T, screen_min_tokens=screen)
+    ids, _, _ = check_layer(run, x, label=f"tiled midpoint screen={screen}")
+    assert np.all(ids[8:400, 0] == 6) and list(ids[7]) == [0, 1, 2, 3]
+    st, _ = run.m.stats()
+    assert st.n_fallback >= 399
+    check_routing(run, x, label="tiled midpoint")
+
+
 def test_bitwise_repeatable_and_permutation_equivariant(dev):
     hl = W.host_layer(SMALL_FP8, seed=508)
     run = Run(SMALL_FP8, hl, dev, max_tokens=32)
