@@ -147,8 +147,8 @@ typedef struct moe_decode_stats {
 typedef enum {
     MOE_STAGE_ROUTE = 0,   /* router logits, top-k softmax, grouping */
     MOE_STAGE_W13 = 1,     /* grouped gate/up projection with the SiLU-gate epilogue */
-    MOE_STAGE_W2 = 2,      /* grouped down projection */
-    MOE_STAGE_COMBINE = 3, /* weighted combine */
+    MOE_STAGE_W2 = 2,      /* grouped down projection (and the combine, where one kernel does both) */
+    MOE_STAGE_COMBINE = 3, /* weighted combine (empty where the down projection combines) */
     MOE_N_STAGES = 4
 } moe_stage;
 

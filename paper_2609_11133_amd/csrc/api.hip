@@ -401,6 +401,15 @@ moe_status moe_decode_forward(moe_decode_t h, void *stream, const void *x, int32
     if (mfma && nv) HIPCHECK(h, launch_w13_nvfp4(L, expert_w, scales, T, k, w.meta, w.tok_of, w, st));
     if (mfma && !nv) HIPCHECK(h, launch_w13_mfma(L, expert_w, scales, T, k, w.meta, w.tok_of, w, st));
     if (prof) prof_mark(h, 2, st);
+    if (mfma && !gemv && w2_combines(L, T, k)) {
+        HIPCHECK(h, launch_w2_combine(L, expert_w, scales, T, k, w.meta, w, y, st));
+        if (prof) {  // the combine is part of the down projection: its stage is empty
+            prof_mark(h, 3, st);
+            prof_mark(h, 4, st);
+            h->prof_n++;
+        }
+        return MOE_OK;
+    }
     if (gemv) HIPCHECK(h, launch_w2(L, expert_w, scales, T, k, w.meta, w.h, w.o, st));
     if (mfma && nv) HIPCHECK(h, launch_w2_nvfp4(L, expert_w, scales, T, k, w.meta, w, st));
     if (mfma && !nv) HIPCHECK(h, launch_w2_mfma(L, expert_w, scales, T, k, w.meta, w, st));

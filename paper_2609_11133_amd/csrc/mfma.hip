@@ -1332,6 +1332,199 @@ __global__ __launch_bounds__(64 * kWideW) __attribute__((amdgpu_waves_per_eu(2))
     }
 }
 
+// ------------------------------------------------------------------ down projection with the combine
+//
+// Small batches: workgroup i owns output rows 16i .. +16 of every pair of the step, so it
+// also combines them and writes y: no expert outputs in memory and no combine launch.  Its
+// waves take the passes (up to eight tokens of one expert) in turn, and each wave's stream
+// of weights (one 16-row tile per pass) runs through a four-slot ring without a break from
+// one pass to the next, where a work item per tile paid a start of its own.  The token
+// columns of the matrix instruction hold both terms of the activation split, the high codes
+// of the pass's tokens in columns 0..7 and the low ones in 8..15, so a K block is one MFMA
+// and one activation fragment; the two halves are added at the end of the pass.  All
+// workgroups walk the experts in the same order, and together read each expert's matrix as
+// one contiguous piece.
+//
+// Measured at one token on the 235B-shaped layer: 15.0 -> 13.0 us for the down projection and
+// the combine together (of 44.1 us per step); rings of six and eight slots and workgroups of
+// four and sixteen waves came out within 1 us.
+
+constexpr int kOwnTok = 8;         // tokens per pass
+constexpr int kOwnChunks = 256;    // chunk records at most
+constexpr int kOwnPairs = 512;     // (token, expert) pairs at most
+constexpr int kOwnW = 8;           // waves per workgroup
+
+// Inclusive prefix sum over the wave with DPP row shifts, then the row totals; returns the
+// wave's total.
+__device__ inline int own_scan(int &v, int lane)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
+    const int t0 = __builtin_amdgcn_readlane(v, 15), t1 = __builtin_amdgcn_readlane(v, 31),
+              t2 = __builtin_amdgcn_readlane(v, 47), t3 = __builtin_amdgcn_readlane(v, 63);
+    const int row = lane >> 4;
+    v += (row >= 1 ? t0 : 0) + (row >= 2 ? t1 : 0) + (row >= 3 ? t2 : 0);
+    return t0 + t1 + t2 + t3;
+}
+
+// Passes of a step at most: one per chunk and one more per eight pairs.
+__host__ __device__ inline int own_max_pass(int E, int P) { return (P < E ? P : E) + (P + kOwnTok - 1) / kOwnTok + 1; }
+
+template <int FMT, bool PK, bool OUTF32>
+__global__ __launch_bounds__(64 * kOwnW) __attribute__((amdgpu_waves_per_eu(4))) void w2_own_kernel(
+    const uint8_t *__restrict__ ew, const uint8_t *__restrict__ es, const int32_t *__restrict__ meta,
+    const int32_t *__restrict__ slot_of, const float *__restrict__ wts, const uint8_t *__restrict__ hs_hi,
+    const uint8_t *__restrict__ hs_lo, const uint8_t *__restrict__ he_hi, const uint8_t *__restrict__ he_lo,
+    void *__restrict__ y, int T, int k, int H, int I, int E, size_t ewb, size_t esb)
+{
+    constexpr int W = kOwnW, R = 4;  // waves, ring slots
+    extern __shared__ __attribute__((aligned(16))) float own_lds[];
+    __shared__ int s_np;
+    const int P = T * k;
+    f32x4 *o = reinterpret_cast<f32x4 *>(own_lds);              // [P][4]: the pair's 16 rows
+    int *s_slot = reinterpret_cast<int *>(own_lds) + 16 * P;    // [P]
+    float *s_wt = own_lds + 17 * P;                             // [P]
+    uint32_t *s_pass = reinterpret_cast<uint32_t *>(own_lds) + 18 * P;  // expert | tokens << 10 | first slot << 16
+    const MetaIdx mi{E};
+    const int4 *recs = reinterpret_cast<const int4 *>(meta + mi.chunk_rec());
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row0 = blockIdx.x * 16, KB = I / 128;
+
+    // the step's passes in expert order, and the combine's slots and weights, in LDS
+    if (wave == 0) {
+        const int n = meta[mi.n_mfma_chunks()];
+        int4 rc[kOwnChunks / 64];  // records past the list are not used
+#pragma unroll
+        for (int u = 0; u < kOwnChunks / 64; ++u) rc[u] = recs[min(64 * u + lane, P + E - 1 < kOwnChunks ? P + E - 1 : kOwnChunks - 1)];
+        int before = 0;
+#pragma unroll
+        for (int u = 0; u < kOwnChunks / 64; ++u) {
+            const int cnt = 64 * u + lane < n ? (rc[u].z + kOwnTok - 1) / kOwnTok : 0;
+            int inc = cnt;
+            const int tot = own_scan(inc, lane);
+            for (int c = 0; c < cnt; ++c)
+                s_pass[before + inc - cnt + c] = (uint32_t)rc[u].x | (uint32_t)min(kOwnTok, rc[u].z - kOwnTok * c) << 10 |
+                                                 (uint32_t)(rc[u].y + kOwnTok * c) << 16;
+            before += tot;
+        }
+        if (lane == 0) s_np = before;
+    } else {
+        for (int i = tid - 64; i < P; i += 64 * (W - 1)) {
+            s_slot[i] = slot_of[i];
+            s_wt[i] = wts[i];
+        }
+    }
+    __syncthreads();
+    const int np = __builtin_amdgcn_readfirstlane(s_np);
+    const int mine = np > wave ? (np - wave + W - 1) / W : 0;  // this wave's passes: wave, wave + W, ...
+
+    const uint32_t lo_off = (uint32_t)(hs_lo - hs_hi), elo_off = (uint32_t)(he_lo - he_hi);
+    const __amdgpu_buffer_rsrc_t hr = raw_rsrc(hs_hi, lo_off + (uint32_t)P * I);
+    const __amdgpu_buffer_rsrc_t er = raw_rsrc(he_hi, elo_off + (uint32_t)P * (I / 32));
+    const size_t rowb = FMT == 0 ? (size_t)I : (size_t)I / 2, w2off = FMT == 0 ? (size_t)2 * I * H : (size_t)I * H;
+    struct {
+        const uint8_t *arow, *erow;
+        const float *sblk;
+        uint32_t voff, eoff;
+        int i, kb;
+    } L;  // the pass whose blocks are being loaded
+    auto pass = [&](int i) { return (uint32_t)__builtin_amdgcn_readfirstlane(s_pass[wave + W * i]); };
+    auto open = [&](int i) {
+        const uint32_t ps = pass(i);
+        const int e = ps & 1023, mc = (ps >> 10) & 15, slot0 = ps >> 16;
+        const uint8_t *we = ew + (size_t)e * ewb + w2off, *se = es + (size_t)e * esb;
+        L.arow = wlane<PK>(we, row0, rowb, lane);
+        L.erow = se + (size_t)2 * I * (H / 32) + (size_t)(row0 + (PK ? 0 : r)) * (I / 32);
+        L.sblk = (const float *)se + (size_t)2 * (I / 128) * (H / 128) + (size_t)(row0 / 128) * (I / 128);
+        const uint32_t row = slot0 + (r & 7);
+        const bool live = (r & 7) < mc;
+        L.voff = live ? (r < 8 ? 0u : lo_off) + row * (uint32_t)I + 16u * g : kOutOfRange;
+        L.eoff = live ? (r < 8 ? 0u : elo_off) + row * (uint32_t)(I / 32) : kOutOfRange;
+        L.i = i;
+        L.kb = 0;
+    };
+    i32x8 A[R], Bf[R];
+    int EA[R];
+    uint32_t X[R];
+    float sc[R];
+    // the next block of the wave's stream into a ring slot (past its end: the last block again)
+    auto load = [&](int slot) {
+        A[slot] = wfrag<FMT, PK>(L.arow, L.kb, g);
+        Bf[slot] = frag_buf(hr, L.voff, L.kb * 128);
+        X[slot] = __builtin_amdgcn_raw_buffer_load_b32(er, L.eoff, L.kb * 4, 0);
+        if constexpr (FMT == 0) {
+            EA[slot] = 127;
+            sc[slot] = wide_const(L.sblk + L.kb);
+        } else {
+            EA[slot] = PK ? e8m0_packed(L.erow, L.kb, KB, lane) : L.erow[L.kb * 4 + g];
+        }
+        if (L.kb + 1 < KB)
+            ++L.kb;
+        else if (L.i + 1 < mine)
+            open(L.i + 1);
+    };
+    if (mine) {
+        open(0);
+#pragma unroll
+        for (int u = 0; u < R - 1; ++u) {
+            load(u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        int ci = 0, ckb = 0;
+        const int nb = mine * KB;
+        for (int n = 0; n < nb; n += R) {
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                load((u + R - 1) % R);
+                __builtin_amdgcn_sched_barrier(0);
+                if (n + u < nb) {
+                    const int eb = (int)__builtin_amdgcn_ubfe(X[u], 8 * g, 8);
+                    if constexpr (FMT == 0) {
+                        f32x4 t = {0.f, 0.f, 0.f, 0.f};
+                        t = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A[u], Bf[u], t, 0, 0, 0, 127, 0, eb);
+                        acc += sc[u] * t;
+                    } else {
+                        acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A[u], Bf[u], acc, 4, 0, 0, EA[u], 0, eb);
+                    }
+                    if (++ckb == KB) {  // the pass is done: lane (r, g) has rows 4g.. of column r
+                        const uint32_t ps = pass(ci);
+                        f32x4 v;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) v[c] = acc[c] + __shfl_xor(acc[c], 8);
+                        if (r < (int)((ps >> 10) & 15)) o[((ps >> 16) + r) * 4 + g] = v;
+                        acc = (f32x4){0.f, 0.f, 0.f, 0.f};
+                        ckb = 0;
+                        ++ci;
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    // y: four rows of a token per thread, choices in rank order
+    for (int i = tid; i < 4 * T; i += 64 * W) {
+        const int t = i >> 2, q = i & 3;
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < k; ++j) {
+            const f32x4 v = o[s_slot[t * k + j] * 4 + q];
+            const float w = s_wt[t * k + j];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) a[c] = fmaf(w, v[c], a[c]);
+        }
+        if constexpr (OUTF32) {
+            *reinterpret_cast<f32x4 *>((float *)y + (size_t)t * H + row0 + 4 * q) = a;
+        } else {
+            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+            *reinterpret_cast<uint2 *>((uint16_t *)y + (size_t)t * H + row0 + 4 * q) =
+                __builtin_bit_cast(uint2, __builtin_convertvector(a, bf16x4));
+        }
+    }
+}
+
 // Waves per workgroup of the staged kernels.  FP8 weights stream at 4 waves and two
 // workgroups per CU: eight waves per CU hold the HBM stream at its best, and more
 // waves per CU slowed it (the 235B- and 480B-shaped layers lost 9-18%).  E2M1
@@ -1583,6 +1776,46 @@ hipError_t launch_w2_mfma(const Layer &L, const void *expert_w, const void *scal
                          : w2_launch<0, false>(L, ew, es, T, k, meta, ws, st);
     return L.wlayout ? w2_launch<1, true>(L, ew, es, T, k, meta, ws, st)
                      : w2_launch<1, false>(L, ew, es, T, k, meta, ws, st);
+}
+
+// The owner kernel saves a launch and the expert outputs' round trip, but a CU streams no
+// more than about 24 GB/s through it, so it needs an even share of the rows on every CU, or
+// so few pairs that launches and latency are the cost.  Step us, other kernels / this one:
+// one token, 235B-shaped FP8 44.1 / 42.1, MXFP4 42.1 / 40.3, H 2048 28.3 / 26.2, H 1024 23.2 /
+// 21.8, but 384 workgroups on 256 CUs (H 6144) 39.3 / 40.4; 24 pairs, H 2048 45.5 / 46.2, H
+// 1024 28.2 / 29.6.  With 256 workgroups (H 4096) and FP8 weights whose rows are too short for
+// the staged kernel it stays ahead: 235B-shaped T=4 106.0 / 104.7, T=32 343 / 339, T=64 equal,
+// row-major T=16 314 / 310; MXFP4 T=4 73.0 / 76.2.
+bool w2_combines(const Layer &L, int T, int k)
+{
+    const long pairs = (long)T * k, active = pairs < L.E ? pairs : L.E;
+    if (L.wfmt == 2 || pairs > kOwnPairs || active + (pairs + kMfmaChunk - 1) / kMfmaChunk > kOwnChunks ||
+        chunk_tokens(L, T, k) != kMfmaChunk)
+        return false;
+    return (pairs <= 8 && L.H / 16 <= 256) || (L.wfmt == 0 && (L.H / 16) % 256 == 0 && L.I < 2048);
+}
+
+template <int FMT, bool PK, bool OUTF32>
+static hipError_t w2_own_launch(const Layer &L, const uint8_t *ew, const uint8_t *es, int T, int k, const int32_t *meta,
+                                const Workspace &ws, void *y, hipStream_t st)
+{
+    const int P = T * k;
+    const size_t lds = sizeof(float) * (18 * (size_t)P + own_max_pass(L.E, P));
+    w2_own_kernel<FMT, PK, OUTF32><<<L.H / 16, 64 * kOwnW, lds, st>>>(ew, es, meta, ws.slot_of, ws.wts, ws.hs_hi, ws.hs_lo,
+                                                                      ws.he_hi, ws.he_lo, y, T, k, L.H, L.I, L.E,
+                                                                      L.expert_w_bytes, L.expert_s_bytes);
+    return hipGetLastError();
+}
+
+hipError_t launch_w2_combine(const Layer &L, const void *expert_w, const void *scales, int T, int k, const int32_t *meta,
+                             const Workspace &ws, void *y, hipStream_t st)
+{
+    const uint8_t *ew = (const uint8_t *)expert_w, *es = (const uint8_t *)scales;
+#define OWN(F, PK) (L.act_bf16 ? w2_own_launch<F, PK, false>(L, ew, es, T, k, meta, ws, y, st)     \
+                               : w2_own_launch<F, PK, true>(L, ew, es, T, k, meta, ws, y, st))
+    if (L.wfmt == 0) return L.wlayout ? OWN(0, true) : OWN(0, false);
+    return L.wlayout ? OWN(1, true) : OWN(1, false);
+#undef OWN
 }
 
 hipError_t launch_pack_scales(const Layer &L, const void *src, void *dst, int n_experts, hipStream_t st)

@@ -136,6 +136,11 @@ hipError_t launch_w13_nvfp4(const Layer &L, const void *expert_w, const void *sc
                             const int32_t *meta, const int32_t *tok_of, const Workspace &ws, hipStream_t st);
 hipError_t launch_w2_nvfp4(const Layer &L, const void *expert_w, const void *scales, int T, int k,
                            const int32_t *meta, const Workspace &ws, hipStream_t st);
+// Whether the step's down projection (every expert on MFMA tiles) also combines and
+// writes y (launch_w2_combine, in place of launch_w2_mfma and launch_combine).
+bool w2_combines(const Layer &L, int T, int k);
+hipError_t launch_w2_combine(const Layer &L, const void *expert_w, const void *scales, int T, int k, const int32_t *meta,
+                             const Workspace &ws, void *y, hipStream_t st);
 hipError_t launch_combine(const Layer &L, int T, int k, const int32_t *slot_of, const float *wts, const float *o,
                           void *y, hipStream_t st);
 

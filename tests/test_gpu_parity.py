@@ -602,6 +602,30 @@ def test_nvfp4_wide_chunks(dev, cfg, layout):
     assert any(1 <= n <= 32 for n in sizes) and any(33 <= n <= 64 for n in sizes)
 
 
+# (layer, top-k, tokens): the down projection that combines, taken up to 8 pairs, and for FP8
+# layers of H = 4096 and I < 2048 up to 512; K block counts from 1 to 12 around its ring of
+# four, passes of up to eight tokens (the skewed batches need several per expert), and the
+# token and pair counts next to its limits
+OWN = [(LayerConfig("own-k1", 256, 8, 2, 128, "f32", "f32", "fp8", None, []), (1, 3, 4, 5)),
+       (LayerConfig("own-k5", 640, 16, 4, 640, "bf16", "bf16", "fp8", "normal:0.5", []), (1, 2, 3)),
+       (LayerConfig("own-mx-k6", 1024, 8, 1, 768, "bf16", "bf16", "mxfp4", "zipf:1.1", []), (1, 7, 8, 9)),
+       (LayerConfig("own-mx-k4", 512, 4, 4, 512, "f32", "bf16", "mxfp4", "zipf:1.1", []), (1, 2)),
+       (LayerConfig("own-h4096", 4096, 16, 4, 384, "bf16", "bf16", "fp8", "zipf:1.1", []), (9, 40, 83, 128, 129)),
+       (LayerConfig("own-h4096-k3", 4096, 24, 3, 1152, "f32", "bf16", "fp8", None, []), (17,))]
+
+
+@pytest.mark.parametrize("cfg,tokens", OWN, ids=lambda v: v.name if isinstance(v, LayerConfig) else "")
+@pytest.mark.parametrize("layout", [0, 1], ids=["rows", "packed"])
+def test_down_projection_with_combine(dev, cfg, tokens, layout):
+    hl = W.host_layer(cfg, seed=631)
+    run = Run(cfg, hl, dev, max_tokens=max(tokens), weight_layout=layout)
+    for T in tokens:
+        check_layer(run, W.host_x(cfg, T, seed=631 + T), label=f"{cfg.name} T={T}")
+        x = W.host_x(cfg, T, seed=900 + T)
+        a, b = run.forward(x), run.forward(x)
+        assert all(np.array_equal(p, q) for p, q in zip(a, b)), "not repeatable"
+
+
 PK_NV_WIDE = LayerConfig("pk-nv-wide", 1024, 16, 8, 1024, "bf16", "bf16", "nvfp4", "zipf:1.1", [])
 
 
