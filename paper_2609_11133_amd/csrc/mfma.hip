@@ -19,6 +19,7 @@
 
 #include "fp8split.h"
 #include "moe_internal.h"
+#include "own.h"
 
 namespace moe {
 namespace {
@@ -1350,27 +1351,7 @@ __global__ __launch_bounds__(64 * kWideW) __attribute__((amdgpu_waves_per_eu(2))
 // four and sixteen waves came out within 1 us.
 
 constexpr int kOwnTok = 8;         // tokens per pass
-constexpr int kOwnChunks = 256;    // chunk records at most
-constexpr int kOwnPairs = 512;     // (token, expert) pairs at most
 constexpr int kOwnW = 8;           // waves per workgroup
-
-// Inclusive prefix sum over the wave with DPP row shifts, then the row totals; returns the
-// wave's total.
-__device__ inline int own_scan(int &v, int lane)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
-    const int t0 = __builtin_amdgcn_readlane(v, 15), t1 = __builtin_amdgcn_readlane(v, 31),
-              t2 = __builtin_amdgcn_readlane(v, 47), t3 = __builtin_amdgcn_readlane(v, 63);
-    const int row = lane >> 4;
-    v += (row >= 1 ? t0 : 0) + (row >= 2 ? t1 : 0) + (row >= 3 ? t2 : 0);
-    return t0 + t1 + t2 + t3;
-}
-
-// Passes of a step at most: one per chunk and one more per eight pairs.
-__host__ __device__ inline int own_max_pass(int E, int P) { return (P < E ? P : E) + (P + kOwnTok - 1) / kOwnTok + 1; }
 
 template <int FMT, bool PK, bool OUTF32>
 __global__ __launch_bounds__(64 * kOwnW) __attribute__((amdgpu_waves_per_eu(4))) void w2_own_kernel(
@@ -1383,42 +1364,11 @@ __global__ __launch_bounds__(64 * kOwnW) __attribute__((amdgpu_waves_per_eu(4)))
     extern __shared__ __attribute__((aligned(16))) float own_lds[];
     __shared__ int s_np;
     const int P = T * k;
-    f32x4 *o = reinterpret_cast<f32x4 *>(own_lds);              // [P][4]: the pair's 16 rows
-    int *s_slot = reinterpret_cast<int *>(own_lds) + 16 * P;    // [P]
-    float *s_wt = own_lds + 17 * P;                             // [P]
-    uint32_t *s_pass = reinterpret_cast<uint32_t *>(own_lds) + 18 * P;  // expert | tokens << 10 | first slot << 16
-    const MetaIdx mi{E};
-    const int4 *recs = reinterpret_cast<const int4 *>(meta + mi.chunk_rec());
+    const OwnLds S(own_lds, P);
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row0 = blockIdx.x * 16, KB = I / 128;
-
-    // the step's passes in expert order, and the combine's slots and weights, in LDS
-    if (wave == 0) {
-        const int n = meta[mi.n_mfma_chunks()];
-        int4 rc[kOwnChunks / 64];  // records past the list are not used
-#pragma unroll
-        for (int u = 0; u < kOwnChunks / 64; ++u) rc[u] = recs[min(64 * u + lane, P + E - 1 < kOwnChunks ? P + E - 1 : kOwnChunks - 1)];
-        int before = 0;
-#pragma unroll
-        for (int u = 0; u < kOwnChunks / 64; ++u) {
-            const int cnt = 64 * u + lane < n ? (rc[u].z + kOwnTok - 1) / kOwnTok : 0;
-            int inc = cnt;
-            const int tot = own_scan(inc, lane);
-            for (int c = 0; c < cnt; ++c)
-                s_pass[before + inc - cnt + c] = (uint32_t)rc[u].x | (uint32_t)min(kOwnTok, rc[u].z - kOwnTok * c) << 10 |
-                                                 (uint32_t)(rc[u].y + kOwnTok * c) << 16;
-            before += tot;
-        }
-        if (lane == 0) s_np = before;
-    } else {
-        for (int i = tid - 64; i < P; i += 64 * (W - 1)) {
-            s_slot[i] = slot_of[i];
-            s_wt[i] = wts[i];
-        }
-    }
-    __syncthreads();
-    const int np = __builtin_amdgcn_readfirstlane(s_np);
+    const int np = own_passes<kOwnTok, W>(S, &s_np, meta, slot_of, wts, P, E, wave, tid);
     const int mine = np > wave ? (np - wave + W - 1) / W : 0;  // this wave's passes: wave, wave + W, ...
 
     const uint32_t lo_off = (uint32_t)(hs_lo - hs_hi), elo_off = (uint32_t)(he_lo - he_hi);
@@ -1431,7 +1381,7 @@ __global__ __launch_bounds__(64 * kOwnW) __attribute__((amdgpu_waves_per_eu(4)))
         uint32_t voff, eoff;
         int i, kb;
     } L;  // the pass whose blocks are being loaded
-    auto pass = [&](int i) { return (uint32_t)__builtin_amdgcn_readfirstlane(s_pass[wave + W * i]); };
+    auto pass = [&](int i) { return (uint32_t)__builtin_amdgcn_readfirstlane(S.pass[wave + W * i]); };
     auto open = [&](int i) {
         const uint32_t ps = pass(i);
         const int e = ps & 1023, mc = (ps >> 10) & 15, slot0 = ps >> 16;
@@ -1495,7 +1445,7 @@ __global__ __launch_bounds__(64 * kOwnW) __attribute__((amdgpu_waves_per_eu(4)))
                         f32x4 v;
 #pragma unroll
                         for (int c = 0; c < 4; ++c) v[c] = acc[c] + __shfl_xor(acc[c], 8);
-                        if (r < (int)((ps >> 10) & 15)) o[((ps >> 16) + r) * 4 + g] = v;
+                        if (r < (int)((ps >> 10) & 15)) S.o[((ps >> 16) + r) * 4 + g] = v;
                         acc = (f32x4){0.f, 0.f, 0.f, 0.f};
                         ckb = 0;
                         ++ci;
@@ -1505,24 +1455,7 @@ __global__ __launch_bounds__(64 * kOwnW) __attribute__((amdgpu_waves_per_eu(4)))
         }
     }
     __syncthreads();
-    // y: four rows of a token per thread, choices in rank order
-    for (int i = tid; i < 4 * T; i += 64 * W) {
-        const int t = i >> 2, q = i & 3;
-        f32x4 a = {0.f, 0.f, 0.f, 0.f};
-        for (int j = 0; j < k; ++j) {
-            const f32x4 v = o[s_slot[t * k + j] * 4 + q];
-            const float w = s_wt[t * k + j];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) a[c] = fmaf(w, v[c], a[c]);
-        }
-        if constexpr (OUTF32) {
-            *reinterpret_cast<f32x4 *>((float *)y + (size_t)t * H + row0 + 4 * q) = a;
-        } else {
-            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-            *reinterpret_cast<uint2 *>((uint16_t *)y + (size_t)t * H + row0 + 4 * q) =
-                __builtin_bit_cast(uint2, __builtin_convertvector(a, bf16x4));
-        }
-    }
+    own_combine<W, OUTF32>(S, y, T, k, H, row0, tid);
 }
 
 // Waves per workgroup of the staged kernels.  FP8 weights stream at 4 waves and two
@@ -1786,13 +1719,21 @@ hipError_t launch_w2_mfma(const Layer &L, const void *expert_w, const void *scal
 // 1024 28.2 / 29.6.  With 256 workgroups (H 4096) and FP8 weights whose rows are too short for
 // the staged kernel it stays ahead: 235B-shaped T=4 106.0 / 104.7, T=32 343 / 339, T=64 equal,
 // row-major T=16 314 / 310; MXFP4 T=4 73.0 / 76.2.
+// NVFP4 weights, whose conversion a second pass of an expert repeats: up to 12 tokens, where
+// skewed routing still breaks even, if most CUs have a workgroup: 235B-shaped T=8 111.8 / 106.3
+// and Zipf-skewed 64.5 / 64.0, T=12 143.8 / 139.6 and 71.2 / 71.2, T=24 202.0 / 197.0 but
+// skewed 97.5 / 99.0 (row-major 120 / 130); 240 workgroups T=8 63.6 / 59.8, 208 T=3 32.2 / 29.3;
+// 64 workgroups (H 1024) T=8 63.6 / 78.7, 384 (H 6144) T=8 246 / 253.
 bool w2_combines(const Layer &L, int T, int k)
 {
     const long pairs = (long)T * k, active = pairs < L.E ? pairs : L.E;
-    if (L.wfmt == 2 || pairs > kOwnPairs || active + (pairs + kMfmaChunk - 1) / kMfmaChunk > kOwnChunks ||
+    if (pairs > kOwnPairs || active + (pairs + kMfmaChunk - 1) / kMfmaChunk > kOwnChunks ||
         chunk_tokens(L, T, k) != kMfmaChunk)
         return false;
-    return (pairs <= 8 && L.H / 16 <= 256) || (L.wfmt == 0 && (L.H / 16) % 256 == 0 && L.I < 2048);
+    const int blocks = L.H / 16;
+    if (pairs <= 8 && blocks <= 256) return true;
+    if (L.wfmt == 2) return T <= 12 && (blocks % 256 == 0 || (blocks >= 192 && blocks < 256));
+    return L.wfmt == 0 && blocks % 256 == 0 && L.I < 2048;
 }
 
 template <int FMT, bool PK, bool OUTF32>
@@ -1800,8 +1741,7 @@ static hipError_t w2_own_launch(const Layer &L, const uint8_t *ew, const uint8_t
                                 const Workspace &ws, void *y, hipStream_t st)
 {
     const int P = T * k;
-    const size_t lds = sizeof(float) * (18 * (size_t)P + own_max_pass(L.E, P));
-    w2_own_kernel<FMT, PK, OUTF32><<<L.H / 16, 64 * kOwnW, lds, st>>>(ew, es, meta, ws.slot_of, ws.wts, ws.hs_hi, ws.hs_lo,
+    w2_own_kernel<FMT, PK, OUTF32><<<L.H / 16, 64 * kOwnW, OwnLds::bytes(L.E, P, kOwnTok), st>>>(ew, es, meta, ws.slot_of, ws.wts, ws.hs_hi, ws.hs_lo,
                                                                       ws.he_hi, ws.he_lo, y, T, k, L.H, L.I, L.E,
                                                                       L.expert_w_bytes, L.expert_s_bytes);
     return hipGetLastError();
@@ -1811,6 +1751,7 @@ hipError_t launch_w2_combine(const Layer &L, const void *expert_w, const void *s
                              const Workspace &ws, void *y, hipStream_t st)
 {
     const uint8_t *ew = (const uint8_t *)expert_w, *es = (const uint8_t *)scales;
+    if (L.wfmt == 2) return launch_w2_nvfp4_combine(L, expert_w, scales, T, k, meta, ws, y, st);
 #define OWN(F, PK) (L.act_bf16 ? w2_own_launch<F, PK, false>(L, ew, es, T, k, meta, ws, y, st)     \
                                : w2_own_launch<F, PK, true>(L, ew, es, T, k, meta, ws, y, st))
     if (L.wfmt == 0) return L.wlayout ? OWN(0, true) : OWN(0, false);

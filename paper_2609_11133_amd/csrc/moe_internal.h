@@ -118,7 +118,7 @@ struct RouteParams {
 };
 
 // ---- launchers (all enqueue on `st`, return hipGetLastError())
-// Tokens per MFMA chunk record of a step: kMfmaChunk or kWideChunk.
+// Tokens per MFMA chunk record of a step: kMfmaChunk, kWideChunk or kWideChunk4.
 int chunk_tokens(const Layer &L, int T, int k);
 hipError_t launch_zero(int32_t *p, int n, hipStream_t st);
 hipError_t launch_route(const Layer &L, const RouteParams &P, hipStream_t st);
@@ -141,6 +141,8 @@ hipError_t launch_w2_nvfp4(const Layer &L, const void *expert_w, const void *sca
 bool w2_combines(const Layer &L, int T, int k);
 hipError_t launch_w2_combine(const Layer &L, const void *expert_w, const void *scales, int T, int k, const int32_t *meta,
                              const Workspace &ws, void *y, hipStream_t st);
+hipError_t launch_w2_nvfp4_combine(const Layer &L, const void *expert_w, const void *scales, int T, int k,
+                                   const int32_t *meta, const Workspace &ws, void *y, hipStream_t st);
 hipError_t launch_combine(const Layer &L, int T, int k, const int32_t *slot_of, const float *wts, const float *o,
                           void *y, hipStream_t st);
 

@@ -48,6 +48,7 @@
 #include <type_traits>
 
 #include "moe_internal.h"
+#include "own.h"
 
 namespace moe {
 namespace {
@@ -876,6 +877,147 @@ __global__ __launch_bounds__(64 * kWW) __attribute__((amdgpu_waves_per_eu(2))) v
     }
 }
 
+// ------------------------------------------------------------------ down projection with the combine
+//
+// Small batches, as for FP8 weights (w2_own_kernel in mfma.hip): workgroup i owns output
+// rows 16i .. +16 of every pair and writes y.  A pass holds up to TOK tokens (4 or 8), and
+// the sixteen token columns of the matrix instruction hold 16/TOK K pieces of each (column
+// TOK*q + t: piece q of token t), so two or four loads bring a 256-input block of a pass's
+// activations, where a tile of sixteen tokens takes eight that are mostly empty.  Each piece
+// has an accumulator; of it only the columns that held that piece count, and they are added
+// over the pieces at the end of the pass.  (Masking the other columns' operands to zero
+// instead took 32 more vector instructions per block: 235B-shaped T=8 111.8 -> 106.3 us
+// without it.)  The conversion of the weights is what bounds it: about 170 cycles per block
+// and CU of the 240 that a block takes, so a pass more costs as much as its weights.
+//
+// Step us, w2_nvfp4_kernel and combine_kernel / this one, 235B-shaped layer: T=1 35.5 / 33.7,
+// T=3 63.4 / 60.6, T=8 111.8 / 106.3, T=12 143.8 / 139.6, row-major T=8 158.7 / 146.2.  Twelve
+// and sixteen waves came out within 1 us.
+
+constexpr int kOwn4W = 8;    // waves per workgroup
+
+template <bool PK, int TOK>
+__global__ __launch_bounds__(64 * kOwn4W) __attribute__((amdgpu_waves_per_eu(2))) void w2_nvfp4_own_kernel(
+    const uint8_t *__restrict__ ew, const uint8_t *__restrict__ es, const int32_t *__restrict__ meta,
+    const int32_t *__restrict__ slot_of, const float *__restrict__ wts, const __bf16 *__restrict__ hb,
+    void *__restrict__ y, int T, int k, int H, int I, int E, int gs, size_t ewb, size_t esb)
+{
+    constexpr int W = kOwn4W, R = 4;  // waves, ring slots
+    constexpr int Q = 16 / TOK;    // K pieces side by side in the columns
+    constexpr int NB = 8 / Q;      // activation loads per block
+    extern __shared__ __attribute__((aligned(16))) float own_lds[];
+    __shared__ int s_np;
+    const int P = T * k;
+    const OwnLds O(own_lds, P);
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row0 = blockIdx.x * 16, KB = I / kBlk;
+    const int np = own_passes<TOK, W>(O, &s_np, meta, slot_of, wts, P, E, wave, tid);
+    const int mine = np > wave ? (np - wave + W - 1) / W : 0;  // this wave's passes: wave, wave + W, ...
+
+    const __amdgpu_buffer_rsrc_t hr = raw_rsrc(hb, (uint32_t)P * (uint32_t)I * 2u);
+    const uint32_t slane = (PK && gs ? 16u : 4u) * (uint32_t)lane;
+    struct {
+        const uint8_t *arow, *srow;
+        float td;
+        uint32_t voff;
+        int i, kb;
+    } L;  // the pass whose blocks are being loaded
+    auto pass = [&](int i) { return (uint32_t)__builtin_amdgcn_readfirstlane(O.pass[wave + W * i]); };
+    auto open = [&](int i) {
+        const uint32_t ps = pass(i);
+        const int e = ps & 1023, mc = (ps >> 10) & 15, slot0 = ps >> 16;
+        const uint8_t *se = es + (size_t)e * esb;
+        const int row = row0 + (PK ? 0 : r);
+        L.arow = ew + (size_t)e * ewb + (size_t)I * H + (size_t)row * (I / 2);
+        L.srow = se + 16 + (size_t)2 * I * (H / 16) + (size_t)row * (I / 16);
+        const uint64_t a = (uint64_t)se;
+        const uint64_t b = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)) << 32) |
+                           (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a);
+        L.td = ((const float __attribute__((address_space(4))) *)b)[2];
+        const int t = r % TOK;
+        L.voff = t < mc ? (uint32_t)(slot0 + t) * (uint32_t)I * 2u + 128u * g + 16u * (r / TOK) : kOutOfRange;
+        L.i = i;
+        L.kb = 0;
+    };
+    u32x4v A[R][2], B[R][NB];
+    uint32_t S[R];
+    float td[R];
+    // the next block of the wave's stream into a ring slot (past its end: the last block again)
+    auto load = [&](int slot) {
+        const int kb = L.kb;
+        if constexpr (PK) {
+            const __amdgpu_buffer_rsrc_t tr = uniform_rsrc(L.arow), sr = uniform_rsrc(L.srow);
+            A[slot][0] = __builtin_amdgcn_raw_buffer_load_b128(tr, 16u * lane, kb * 2048, kNonTemporal);
+            A[slot][1] = __builtin_amdgcn_raw_buffer_load_b128(tr, 16u * lane + 1024u, kb * 2048, kNonTemporal);
+            S[slot] = __builtin_amdgcn_raw_buffer_load_b32(sr, slane, gs ? (kb >> 2) * 1024 + (kb & 3) * 4 : kb * 256, 0);
+        } else {
+            const uint8_t *p = L.arow + (size_t)kb * (kBlk / 2) + 32 * g;
+            A[slot][0] = *reinterpret_cast<const u32x4v *>(p);
+            A[slot][1] = *reinterpret_cast<const u32x4v *>(p + 16);
+            S[slot] = *reinterpret_cast<const uint32_t *>(L.srow + (size_t)kb * (kBlk / 16) + 4 * g);
+        }
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+            B[slot][j] = __builtin_amdgcn_raw_buffer_load_b128(hr, L.voff + 16u * Q * j, kb * 512, 0);
+        td[slot] = L.td;
+        if (kb + 1 < KB)
+            ++L.kb;
+        else if (L.i + 1 < mine)
+            open(L.i + 1);
+    };
+    if (mine) {
+        open(0);
+#pragma unroll
+        for (int u = 0; u < R - 1; ++u) {
+            load(u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        f32x4 acc[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) acc[q] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        int ci = 0, ckb = 0;
+        const int nb = mine * KB;
+        for (int n = 0; n < nb; n += R) {
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                load((u + R - 1) % R);
+                __builtin_amdgcn_sched_barrier(0);
+                if (n + u < nb) {
+                    const f32x2 s01 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(S[u], 1.0f, false);
+                    const f32x2 s23 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(S[u], 1.0f, true);
+#pragma unroll
+                    for (int p = 0; p < 8; ++p) {
+                        const u32x4v a = dequant_8(A[u][p / 4][p % 4], p < 2 ? s01.x : p < 4 ? s01.y : p < 6 ? s23.x : s23.y);
+                        acc[p % Q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, B[u][p / Q]), acc[p % Q], 0, 0, 0);
+                    }
+                    if (++ckb == KB) {  // the pass is done: lane (r, g) has rows 4g.. of column r
+                        const uint32_t ps = pass(ci);
+                        f32x4 v;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            float f = acc[0][c];
+#pragma unroll
+                            for (int q = 1; q < Q; ++q) f = r / TOK == q ? acc[q][c] : f;
+#pragma unroll
+                            for (int d = TOK; d < 16; d *= 2) f += __shfl_xor(f, d);
+                            v[c] = f;
+                        }
+                        if (r < (int)((ps >> 10) & 15)) O.o[((ps >> 16) + r) * 4 + g] = td[u] * v;
+#pragma unroll
+                        for (int q = 0; q < Q; ++q) acc[q] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                        ckb = 0;
+                        ++ci;
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    own_combine<W, false>(O, y, T, k, H, row0, tid);
+}
+
 constexpr int kWaves = 4;
 
 // Workgroups for `items_per_chunk` items per chunk record (see mfma_grid in mfma.hip).
@@ -1008,6 +1150,29 @@ hipError_t launch_w2_nvfp4(const Layer &L, const void *expert_w, const void *sca
     // 92.8 -> 91.5, T=127 99.0 -> 97.4; T=1 and T=8 equal.
     if (tile_only(L, T, k)) return w2_nvfp4_launch<8, true>(L, ew, es, T, k, meta, ws, st);
     return w2_nvfp4_launch<kWaves, false>(L, ew, es, T, k, meta, ws, st);
+}
+
+// Passes of four tokens where an expert has no more or is unlikely to (235B-shaped T=8, 64
+// pairs: 106.3 us per step against 108.5 with eight; T=12 140.2 against 139.6).
+// Activations are bf16 with NVFP4 weights (checked at init), and so is y.
+hipError_t launch_w2_nvfp4_combine(const Layer &L, const void *expert_w, const void *scales, int T, int k,
+                                   const int32_t *meta, const Workspace &ws, void *y, hipStream_t st)
+{
+    const uint8_t *ew = (const uint8_t *)expert_w, *es = (const uint8_t *)scales;
+    const size_t lds = OwnLds::bytes(L.E, T * k, 4);
+#define OWN4(PK, TOK)                                                                                                      \
+    w2_nvfp4_own_kernel<PK, TOK><<<L.H / 16, 64 * kOwn4W, lds, st>>>(ew, es, meta, ws.slot_of, ws.wts, (const __bf16 *)ws.hb, y, \
+                                                                T, k, L.H, L.I, L.E, grouped_scales(L, L.I) ? 1 : 0,  \
+                                                                L.expert_w_bytes, L.expert_s_bytes)
+    if (T <= 4 || 2L * T * k <= L.E) {
+        if (L.wlayout) OWN4(true, 4);
+        else OWN4(false, 4);
+    } else {
+        if (L.wlayout) OWN4(true, 8);
+        else OWN4(false, 8);
+    }
+#undef OWN4
+    return hipGetLastError();
 }
 
 }  // namespace moe

@@ -1467,8 +1467,8 @@ hipError_t launch_route(const Layer &L, const RouteParams &P, hipStream_t st)
     A.id_cache = lds + 2 * pairs <= 49152 ? 1 : 0;
     if (A.id_cache) lds += 2 * pairs;
     if (!P.do_group) lds = 0;
-    // Tiled routing above kTilePairs (token, expert) pairs, and for every screened step it
-    // can take: up to 256 experts, 16 choices.  Four slices of the inputs while the tiles are
+    // Tiled routing above kTilePairs (token, expert) pairs, screened steps among them: up to
+    // 256 experts, 16 choices.  Four slices of the inputs while the tiles are
     // at most one per CU, fewer above (235B-shaped NVFP4 layer, step us with 1 / 2 / 4 / 8
     // slices: T=64 264 / 259 / 257 / 258, T=256 318 / 313 / 311 / 322; 480B-shaped T=1000
     // 1,768 / 1,767 / 1,783 / 1,804).
