@@ -1717,8 +1717,10 @@ hipError_t launch_w2_mfma(const Layer &L, const void *expert_w, const void *scal
 // one token, 235B-shaped FP8 44.1 / 42.1, MXFP4 42.1 / 40.3, H 2048 28.3 / 26.2, H 1024 23.2 /
 // 21.8, but 384 workgroups on 256 CUs (H 6144) 39.3 / 40.4; 24 pairs, H 2048 45.5 / 46.2, H
 // 1024 28.2 / 29.6.  With 256 workgroups (H 4096) and FP8 weights whose rows are too short for
-// the staged kernel it stays ahead: 235B-shaped T=4 106.0 / 104.7, T=32 343 / 339, T=64 equal,
-// row-major T=16 314 / 310; MXFP4 T=4 73.0 / 76.2.
+// the staged kernel it stays ahead up to 8 tokens, one pass per expert: 235B-shaped T=4 106.0 /
+// 104.7, T=8 163 / 159, Zipf-skewed T=8 86.9 / 86.0.  Above, an expert's further passes stream
+// its weights again: uniform T=32 343 / 339, but skewed T=12 98.3 / 101, T=16 103 / 108, T=64 209
+// / 234.  MXFP4 T=4 73.0 / 76.2.
 // NVFP4 weights, whose conversion a second pass of an expert repeats: up to 12 tokens, where
 // skewed routing still breaks even, if most CUs have a workgroup: 235B-shaped T=8 111.8 / 106.3
 // and Zipf-skewed 64.5 / 64.0, T=12 143.8 / 139.6 and 71.2 / 71.2, T=24 202.0 / 197.0 but
@@ -1733,7 +1735,7 @@ bool w2_combines(const Layer &L, int T, int k)
     const int blocks = L.H / 16;
     if (pairs <= 8 && blocks <= 256) return true;
     if (L.wfmt == 2) return T <= 12 && (blocks % 256 == 0 || (blocks >= 192 && blocks < 256));
-    return L.wfmt == 0 && blocks % 256 == 0 && L.I < 2048;
+    return L.wfmt == 0 && T <= 8 && blocks % 256 == 0 && L.I < 2048;
 }
 
 template <int FMT, bool PK, bool OUTF32>
@@ -1741,9 +1743,9 @@ static hipError_t w2_own_launch(const Layer &L, const uint8_t *ew, const uint8_t
                                 const Workspace &ws, void *y, hipStream_t st)
 {
     const int P = T * k;
-    w2_own_kernel<FMT, PK, OUTF32><<<L.H / 16, 64 * kOwnW, OwnLds::bytes(L.E, P, kOwnTok), st>>>(ew, es, meta, ws.slot_of, ws.wts, ws.hs_hi, ws.hs_lo,
-                                                                      ws.he_hi, ws.he_lo, y, T, k, L.H, L.I, L.E,
-                                                                      L.expert_w_bytes, L.expert_s_bytes);
+    w2_own_kernel<FMT, PK, OUTF32><<<L.H / 16, 64 * kOwnW, OwnLds::bytes(L.E, P, kOwnTok), st>>>(
+        ew, es, meta, ws.slot_of, ws.wts, ws.hs_hi, ws.hs_lo, ws.he_hi, ws.he_lo, y, T, k, L.H, L.I, L.E, L.expert_w_bytes,
+        L.expert_s_bytes);
     return hipGetLastError();
 }
 
