@@ -76,11 +76,13 @@ __device__ inline float round_dd_to_f32(double hi, double lo)
 // True if every real number within `bound` of v rounds to the same fp32 value r: rounding
 // is monotonic, so it does if both ends of an interval that contains them do (the slack
 // covers the ends' own fp64 rounding).
-__device__ inline bool certain_f32(double v, double bound, float &r)
+// `up` is the value that the upper end rounds to: at least every such number's.
+__device__ inline bool certain_f32(double v, double bound, float &r, float &up)
 {
     const double m = bound + fabs(v) * 0x1p-51;
     r = (float)(v - m);
-    return r == (float)(v + m);
+    up = (float)(v + m);
+    return r == up;
 }
 
 template <typename T>
@@ -302,8 +304,8 @@ __device__ __attribute__((always_inline)) inline int wave_logits(const XT *__res
             const int e = ex[i];
             const double b = bias ? (double)bias[e] : 0.0;
             const double slack = kBf16 ? (double)H * 0x1p-148 : 0.0;
-            float r;
-            if (!certain_f32(si + b, gamma * (ai + fabs(b)) + slack, r)) {
+            float r, up;
+            if (!certain_f32(si + b, gamma * (ai + fabs(b)) + slack, r, up)) {
                 r = wave_logit_exact<XT, WT>(xr, wr + (size_t)e * H, b, H, lane);
                 ++nfb;
             }
@@ -1316,11 +1318,15 @@ __global__ __launch_bounds__(256) void route_tile_kernel(RouteArgs A)
     }
 
     // 3. last workgroup of the token tile, a token per 16-lane row, four to a wave: logits,
-    // top k.  A logit that the bound does not certify matters only if it can reach the
-    // top k: those are recomputed exactly (every one where the logits are asked for) and the
-    // top k taken again, all within the wave.
+    // top k.  A logit that the bound does not certify goes in at the lower end of its
+    // interval, so the k-th largest value is a lower bound of the k-th largest logit, and the
+    // logit matters only if its upper end reaches that value (ends equal to it may tie).
+    // Under cancellation the two ends are many fp32 steps apart.  Those that matter are
+    // recomputed exactly (every one where the logits are asked for) and the top k taken
+    // again, all within the wave; the others stay below the k largest.
     const int tk = 4 * wave + g, t = t0 + tk;
     float *l = (float *)lds + (size_t)tk * E;  // this row's logits
+    float *lu = l + 16 * (size_t)E;            // ... and the upper ends of the uncertain ones
     uint16_t *fb = (uint16_t *)&s_red[wave][0];  // the wave's uncertain logits
     if (lane == 0) s_nfb[wave] = 0;
     if (tid == 0) st_dev(&A.cnt_tok[blockIdx.z * kCounterStride], 0);
@@ -1331,8 +1337,11 @@ __global__ __launch_bounds__(256) void route_tile_kernel(RouteArgs A)
         const double gamma = (double)D * 0x1p-52;
         auto done = [&](int e, double S, double Bd) {
             const double bias = A.bias ? (double)A.bias[e] : 0.0;
-            float c;
-            if (!certain_f32(S + bias, gamma * (Bd + fabs(bias)), c)) fb[atomicAdd(&s_nfb[wave], 1)] = (uint16_t)(g * kTileE + e);
+            float c, up;
+            if (!certain_f32(S + bias, gamma * (Bd + fabs(bias)), c, up)) {
+                fb[atomicAdd(&s_nfb[wave], 1)] = (uint16_t)(g * kTileE + e);
+                lu[e] = up;
+            }
             l[e] = c + 0.0f;  // -0 -> +0
         };
         if (KS == 1)
@@ -1354,9 +1363,7 @@ __global__ __launch_bounds__(256) void route_tile_kernel(RouteArgs A)
             const int fg = __builtin_amdgcn_readfirstlane((int)fb[i] / kTileE);
             const int e = __builtin_amdgcn_readfirstlane((int)fb[i] % kTileE);
             float *lf = (float *)lds + (size_t)(4 * wave + fg) * E + e;
-            // the canonical logit is the value here or a neighbour of it
-            const float up = nextafterf(nextafterf(*lf, INFINITY), INFINITY);
-            if (A.do_group && up < __shfl(last, 16 * fg)) continue;
+            if (A.do_group && lf[16 * (size_t)E] < __shfl(last, 16 * fg)) continue;
             const float c = wave_logit_exact<XT, WT>(x + (size_t)(t0 + 4 * wave + fg) * H, (const WT *)A.wr + (size_t)e * H,
                                                      A.bias ? (double)A.bias[e] : 0.0, H, lane);
             if (lane == 0) *lf = c + 0.0f;
@@ -1478,7 +1485,7 @@ hipError_t launch_route(const Layer &L, const RouteParams &P, hipStream_t st)
         while (ks > 1 && (ks > P.ks_max || ks > L.H / 256)) ks /= 2;
         A.KS = ks;
         A.screened = P.do_group && P.screen && L.act_bf16 && L.router_bf16 ? 1 : 0;
-        const size_t lf = (size_t)16 * L.E * sizeof(float), bytes = lds > lf ? lds : lf;
+        const size_t lf = (size_t)2 * 16 * L.E * sizeof(float), bytes = lds > lf ? lds : lf;  // values, upper ends
         dim3 grid(ks, et, tt), block(256);
         if (L.act_bf16 && L.router_bf16)
             route_tile_kernel<uint16_t, uint16_t><<<grid, block, bytes, st>>>(A);

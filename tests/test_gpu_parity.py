@@ -352,6 +352,56 @@ def test_tiled_routing_degenerate(dev, screen):
     check_routing(run, x, label="tiled midpoint")
 
 
+def _bf16(v):
+    """fp32 values that are bf16 values -> their bits."""
+    u = np.asarray(v, np.float32).view(np.uint32)
+    assert not (u & 0xFFFF).any()
+    return (u >> 16).astype(np.uint16)
+
+
+@pytest.mark.parametrize("screen", [-1, 1], ids=["exact", "screened"])
+def test_tiled_routing_cancellation(dev, screen):
+    """Logits whose products cancel: the fp64 sum's bound spans many fp32 steps there, and
+    the top k has to come from the exact values.  Rows 0..15: equal zeros of different row
+    norms (ties to the lower index); then a tiny positive logit next to certain zeros; then
+    pairs of random products that cancel and leave tiny logits of either sign."""
+    cfg = LayerConfig("tiled-cancel", 512, 16, 4, 256, "bf16", "bf16", "fp8", None, [])
+    hl = W.host_layer(cfg, seed=519)
+    T = 405
+    run = Run(cfg, hl, dev, max_tokens=T, screen_min_tokens=screen)
+
+    def check(x, w, k, label):
+        hl.router_w[:] = _bf16(w)
+        run.rw = W.to_device(hl.router_w, dev)
+        ids, _, _ = check_layer(run, _bf16(x), topk=k, label=f"tiled cancel {label} screen={screen}")
+        check_routing(run, _bf16(x[:401]), topk=k, label=f"tiled cancel {label}")
+        return ids
+
+    x, w = np.zeros((T, cfg.hidden)), np.zeros((16, cfg.hidden))
+    x[:, :2] = 1.0
+    w[:, 0] = 2.0 - np.arange(16) / 16
+    w[:, 1] = -w[:, 0]
+    assert np.all(check(x, w, 4, "zeros") == np.arange(4))
+
+    x[:, :3] = 2.0 ** 24, 2.0 ** 24, 1.0
+    w[:] = 0
+    w[1, :3] = 1.0, -1.0, 2.0 ** -21
+    assert np.all(check(x, w, 1, "tiny") == 1)
+
+    r = np.random.default_rng(519)
+    m = lambda n: (1 + r.integers(0, 128, n) / 128) * np.exp2(r.integers(-4, 5, n)) * r.choice([-1, 1], n)  # noqa: E731
+    x = np.empty((T, cfg.hidden))
+    x[:, 0::2] = m((T, cfg.hidden // 2))
+    x[:, 1::2] = x[:, 0::2]
+    w = np.empty((16, cfg.hidden))
+    w[:, 0::2] = m((16, cfg.hidden // 2)) * np.exp2(r.integers(0, 12, 16))[:, None]  # norms of a wide range
+    w[:, 1::2] = -w[:, 0::2]
+    x[:, -1] = 2.0 ** -20
+    x[:, -2] = 0
+    for k in (1, 3, 4):
+        check(x, w, k, f"pairs k={k}")
+
+
 def test_bitwise_repeatable_and_permutation_equivariant(dev):
     hl = W.host_layer(SMALL_FP8, seed=508)
     run = Run(SMALL_FP8, hl, dev, max_tokens=32)
