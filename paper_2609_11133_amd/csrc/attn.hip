@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "../../include/attn_decode.h"
+#include "attn_grid.h"
 
 namespace attn {
 namespace {
@@ -99,27 +100,27 @@ __device__ inline bf16x8 as_bf16x8(const u32x4v &u) { return __builtin_bit_cast(
 // 9.3, of 512 23.7 / 11.7, of 2048 30.4 / 26.4, of 32768 290 / 288.  (A grid of at most
 // 1024 workgroups that look their items up in the batch's lengths has no idle ones, but
 // the look-up added 2.4 us to every workgroup's chain.)
+//
+// Arguments are read from host memory, 64 bytes at a time; what the address of ctx[b] needs
+// lies in both of the first two such lines (rot and ctx), so that the first wait brings both.
 template <bool FUSED>
-__global__ __launch_bounds__(256) void attn_split_kernel(const uint16_t *__restrict__ q,
-                                                         const uint16_t *__restrict__ kc,
-                                                         const uint16_t *__restrict__ vc, int64_t n_pages,
-                                                         const int32_t *__restrict__ block_table, int max_pages,
-                                                         const int32_t *__restrict__ ctx, int Hkv, int G,
-                                                         float scale_log2, float *__restrict__ po,
-                                                         float *__restrict__ pml, int S, int R,
-                                                         int32_t *__restrict__ cnt, uint16_t *__restrict__ out)
+__global__ __launch_bounds__(256) void attn_split_kernel(
+    RowRotation rot, int slots, int S, int max_pages, const uint16_t *__restrict__ q, const uint16_t *__restrict__ kc,
+    const uint16_t *__restrict__ vc, int64_t n_pages, const int32_t *__restrict__ block_table,
+    const int32_t *__restrict__ ctx, int Hkv, int G, float scale_log2, float *__restrict__ po, float *__restrict__ pml,
+    int32_t *__restrict__ cnt, uint16_t *__restrict__ out)
 {
     __shared__ float s_max[2][kWaves][16], s_sum[kWaves][16];
     __shared__ f32x4 red[kWaves][kDT][64];
     __shared__ float s_w[FUSED ? kFusedSplits : 1][16], s_den[16];
     __shared__ int s_last;
-    const int c = blockIdx.z, g = blockIdx.x, b = blockIdx.y;
+    const int c = blockIdx.z, g = blockIdx.x, b = rot.sequence(blockIdx.y, c);
     const int L = min(max(ctx[b], 0), max_pages * kP);
-    // FUSED: a sequence of at most `slots` chunks (the grid's splits) takes one split per
-    // chunk, a longer one spreads its chunks over the configuration's S splits.  So a short
-    // context in a configuration sized for long ones still gets one workgroup per chunk,
-    // and a sequence's result depends on its own length only, never on its batch.
-    const int slots = gridDim.z;  // partials per (b, g)
+    // FUSED: a sequence of at most `slots` chunks (the grid's splits, and the partials per
+    // (b, g)) takes one split per chunk, a longer one spreads its chunks over S splits.  So a
+    // short context in a configuration sized for long ones still gets one workgroup per
+    // chunk, and a sequence's result depends on its own length only, never on its batch.
+    int R = 1;
     if (FUSED) {
         const int nc = (L + kChunk - 1) / kChunk;
         R = nc <= slots ? 1 : (nc + S - 1) / S;
@@ -626,16 +627,18 @@ extern "C" int attn_decode_forward(const attn_decode_config *cfg, void *workspac
         const int grid_s = grid_splits(cfg, S);
         if (S > partial_slots(cfg)) return fail(ATTN_ERR_INVALID, "internal: %d splits exceed the workspace", S);
         attn_split_kernel<true><<<dim3(Hkv, batch, grid_s), 256, 0, st>>>(
-            (const uint16_t *)q, (const uint16_t *)k_cache, (const uint16_t *)v_cache, n_pages, block_table,
-            cfg->max_pages_per_seq, ctx_lens, Hkv, G, scale * kLog2e, po, pml, S, R, cnt, (uint16_t *)out);
+            RowRotation(Hkv, batch), grid_s, S, cfg->max_pages_per_seq,
+            (const uint16_t *)q, (const uint16_t *)k_cache, (const uint16_t *)v_cache, n_pages, block_table, ctx_lens,
+            Hkv, G, scale * kLog2e, po, pml, cnt, (uint16_t *)out);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(ATTN_ERR_HIP, "split kernel launch: %s", hipGetErrorString(e));
         return ATTN_OK;
     }
     const int S = max_splits(cfg);
     attn_split_kernel<false><<<dim3(Hkv, batch, S), 256, 0, st>>>(
-        (const uint16_t *)q, (const uint16_t *)k_cache, (const uint16_t *)v_cache, n_pages, block_table,
-        cfg->max_pages_per_seq, ctx_lens, Hkv, G, scale * kLog2e, po, pml, S, 1, cnt, (uint16_t *)out);
+        RowRotation(Hkv, batch), S, S, cfg->max_pages_per_seq, (const uint16_t *)q, (const uint16_t *)k_cache,
+        (const uint16_t *)v_cache, n_pages, block_table, ctx_lens, Hkv, G, scale * kLog2e, po, pml, cnt,
+        (uint16_t *)out);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ATTN_ERR_HIP, "split kernel launch: %s", hipGetErrorString(e));
     attn_combine_kernel<<<dim3(G, Hkv, batch), 128, 0, st>>>(po, pml, ctx_lens, cfg->max_pages_per_seq, Hkv, G, S,
