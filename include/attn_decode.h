@@ -65,7 +65,8 @@ typedef struct attn_decode_config {
                                   in large batches, and within the limit) takes one per
                                   split; a longer one walks R = ceil(its own pieces / S)
                                   consecutive pieces per workgroup (online softmax across
-                                  them).  The split kernel merges the splits itself (its
+                                  them; that few in S's place where S of every row would
+                                  just overflow one round).  The split kernel merges the splits itself (its
                                   last workgroup per sequence and key/value head).  0 =
                                   library default (16, or 32 where n_kv_heads * max_batch
                                   is below 16), at most 16; negative = one piece per split,

@@ -56,7 +56,7 @@ constexpr int kDT = kD / 16;               // 16-column tiles of the output
 constexpr float kLog2e = 1.44269504088896340736f;
 constexpr int kRawBufferWord3 = 0x00020000;  // untyped 32-bit data format, no swizzle
 constexpr int kFusedSplits = 32;             // splits merged inside the split kernel, at most
-constexpr long kGridWorkgroups = 3072;       // workgroups up to which the grid takes more splits
+constexpr long kGridWorkgroups = 1792;       // workgroups up to which the grid takes more splits
 constexpr int kUserSplits = 16;              // ... and at most by fused_merge_max_splits
 
 // Device-coherent accesses for the hand-off between workgroups (relaxed atomics at agent
@@ -548,16 +548,32 @@ int chunks_per_split(const attn_decode_config *c)
 // lengths the few long sequences are the longest chain: 24 sequences of the standard mix
 // on 4 heads (S = 8) 18.1 us at R = ceil(chunks / 8), 15.3 with up to 12 splits; where all
 // are that long it is even at 12 chunks (40.5 / 41.0) and loses at 16 (46.7 / 52.8).  Every
-// split is one more workgroup per row that short sequences leave idle, so many rows take
-// fewer, and rows that fill the slots (two workgroups per CU) by themselves none: 96
-// sequences of 512 tokens on 8 heads 42.2 us with one split each, 48.8 with two.
+// split is one more workgroup per row, idle where the sequence is short and a round of its
+// own where all are long, so many rows take fewer: at most kGridWorkgroups, and two from 385
+// rows on, where S is 1 and one round holds every sequence.  Step us with up to 3072
+// workgroups / this: contexts of one length, 256 rows of 3072 tokens 85 / 73, 384 of 2048
+// 83 / 72, 504 of 1536 81 / 66, 448 of 768 37 / 31; agent contexts, 384 rows 51 / 47; chat
+// contexts, 320 rows 29.0 / 27.4, 384 rows 34.2 / 34.8.  Rows that fill the slots (two
+// workgroups per CU) by themselves take S: 96 sequences of 512 tokens on 8 heads 42.2 us with
+// one split each, 48.8 with two.
 int grid_splits(const attn_decode_config *c, int S)
 {
     const long rows = (long)c->n_kv_heads * c->max_batch;
-    if (rows >= kGridWorkgroups / 6) return S;
-    const long per = kGridWorkgroups / rows;
+    if (rows >= 512) return S;
+    const long per = rows > 384 ? 2 : kGridWorkgroups / rows;
     const int few = per > 12 ? 12 : (int)per, slots = partial_slots(c);
     return S > few ? S : (few < slots ? few : slots);
+}
+
+// Splits that a longer sequence spreads its chunks over: S, but the grid's where S splits of
+// every row would run just over one round of resident workgroups (by a quarter at most),
+// since the second round is nearly empty: contexts of one length, S / the grid's splits, 288
+// rows of 8192 tokens 246 / 224 us, 200 of 3072 65.6 / 59.5, 320 of 3072 99.5 / 95.9; but 192
+// of 8192 (1.5 rounds) 144 / 150, 256 of 6000 141 / 148.
+int walk_splits(const attn_decode_config *c, int S, int grid)
+{
+    const long wgs = (long)c->n_kv_heads * c->max_batch * S, slots = 2L * compute_units();
+    return wgs > slots && wgs <= slots * 5 / 4 ? grid : S;
 }
 
 bool aligned(const void *p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
@@ -627,7 +643,7 @@ extern "C" int attn_decode_forward(const attn_decode_config *cfg, void *workspac
         const int grid_s = grid_splits(cfg, S);
         if (S > partial_slots(cfg)) return fail(ATTN_ERR_INVALID, "internal: %d splits exceed the workspace", S);
         attn_split_kernel<true><<<dim3(Hkv, batch, grid_s), 256, 0, st>>>(
-            RowRotation(Hkv, batch), grid_s, S, cfg->max_pages_per_seq,
+            RowRotation(Hkv, batch), grid_s, walk_splits(cfg, S, grid_s), cfg->max_pages_per_seq,
             (const uint16_t *)q, (const uint16_t *)k_cache, (const uint16_t *)v_cache, n_pages, block_table, ctx_lens,
             Hkv, G, scale * kLog2e, po, pml, cnt, (uint16_t *)out);
         const hipError_t e = hipGetLastError();

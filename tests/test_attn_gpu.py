@@ -118,11 +118,14 @@ def test_fused_merge_matches_two_kernels(dev, name):
 # (query heads, key/value heads, block-table row in pages, lengths): up to 32 splits where the
 # rows are fewer than 16 (one chunk per split, then two); 24 sequences of 4 heads whose row
 # of 16 chunks has 8 splits (one chunk per split up to 12 chunks, two from 13); 128 rows with
-# a grid of 12; 520 rows, which keep the configuration's one split
+# a grid of 12; 520 rows, which keep the configuration's one split; 288 rows (a grid of 6,
+# which longer sequences spread over too); 392 rows (a grid of two, then one split)
 SPLIT_RULES = [(4, 1, 640, [8192, 4097, 8193, 10240, 0, 17 * 256]),
                (16, 4, 256, [3072, 3073, 2049, 4096, 1, 2048] + [100] * 18),
                (8, 8, 256, [4096, 2817, 3072, 300] + [16] * 12),
-               (8, 8, 48, [768, 257, 256, 5] + [16] * 61)]
+               (8, 8, 48, [768, 257, 256, 5] + [16] * 61),
+               (8, 8, 256, [1537, 4096, 1536, 3073, 1793] + [16] * 31),
+               (8, 8, 128, [513, 2048, 512, 257, 0] + [16] * 44)]
 
 
 @pytest.mark.parametrize("hq,hkv,pages,lens", SPLIT_RULES, ids=lambda v: "" if isinstance(v, list) else str(v))
