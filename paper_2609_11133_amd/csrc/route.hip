@@ -1114,15 +1114,12 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 __device__ inline void sync_wave() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // Maximum / minimum over each 16-lane row, the same in all its lanes.
-__device__ inline float row_max(float v)
+__device__ inline uint32_t row_max(uint32_t v)
 {
-    const auto d = [](float x, auto c) {
-        return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), decltype(c)::value, 0xF, 0xF, false));
-    };
-    v = fmaxf(v, d(v, std::integral_constant<int, 0xB1>{}));   // quad_perm [1,0,3,2]
-    v = fmaxf(v, d(v, std::integral_constant<int, 0x4E>{}));   // quad_perm [2,3,0,1]
-    v = fmaxf(v, d(v, std::integral_constant<int, 0x141>{}));  // row_half_mirror
-    return fmaxf(v, d(v, std::integral_constant<int, 0x140>{}));  // row_mirror
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0u, v, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0u, v, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0u, v, 0x141, 0xF, 0xF, false));  // row_half_mirror
+    return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0u, v, 0x140, 0xF, 0xF, false));  // row_mirror
 }
 __device__ inline int row_min(int v)
 {
@@ -1134,32 +1131,34 @@ __device__ inline int row_min(int v)
 
 // The k largest logits of the token of each 16-lane row, ties to the lower expert: lane
 // j < k of the row gets choice j (its logit and expert), every lane the last choice's logit
-// and the number of unchosen experts tied with it.
+// and the number of unchosen experts tied with it.  Keys are the logits' ordered bits; 0
+// stands for a chosen expert or none, below every logit's key, an infinity's and a NaN's
+// too, so the choices are k different experts below E whatever the logits are (k <= E).
 template <int V>
 __device__ __attribute__((always_inline)) inline void tile_topk(const float *l, int E, int k, int j, float &lj, int &ej,
                                                                 float &last, int &tied)
 {
-    float val[V];
+    uint32_t key[V], m = 0u;
 #pragma unroll
-    for (int v = 0; v < V; ++v) val[v] = 16 * v + j < E ? l[16 * v + j] : -INFINITY;
-    lj = 0.f, ej = 0, last = 0.f;
+    for (int v = 0; v < V; ++v) key[v] = 16 * v + j < E ? max(ordered_bits(l[16 * v + j]), 1u) : 0u;
+    lj = 0.f, ej = 0;
     for (int c = 0; c < k; ++c) {
-        float m = val[0];
+        m = key[0];
 #pragma unroll
-        for (int v = 1; v < V; ++v) m = fmaxf(m, val[v]);
+        for (int v = 1; v < V; ++v) m = max(m, key[v]);
         m = row_max(m);
         int e = INT_MAX;
 #pragma unroll
-        for (int v = V - 1; v >= 0; --v) e = val[v] == m ? 16 * v + j : e;
+        for (int v = V - 1; v >= 0; --v) e = key[v] == m ? 16 * v + j : e;
         e = row_min(e);
-        if (j == c) lj = m, ej = e;
+        if (j == c) lj = from_ordered(m), ej = e;
 #pragma unroll
-        for (int v = 0; v < V; ++v) val[v] = 16 * v + j == e ? -INFINITY : val[v];
-        last = m;
+        for (int v = 0; v < V; ++v) key[v] = 16 * v + j == e ? 0u : key[v];
     }
+    last = from_ordered(m);
     tied = 0;
 #pragma unroll
-    for (int v = 0; v < V; ++v) tied += val[v] == last ? 1 : 0;
+    for (int v = 0; v < V; ++v) tied += key[v] == m ? 1 : 0;
 }
 
 __device__ __attribute__((always_inline)) inline void tile_topk_any(const float *l, int E, int k, int j, float &lj, int &ej,

@@ -402,6 +402,55 @@ def test_tiled_routing_cancellation(dev, screen):
         check(x, w, k, f"pairs k={k}")
 
 
+@pytest.mark.parametrize("E,k,T", [(128, 8, 51), (160, 16, 41), (20, 4, 321)], ids=lambda v: str(v))
+@pytest.mark.parametrize("screen", [-1, 1], ids=["exact", "screened"])
+def test_tiled_routing_unordered_rows(dev, E, k, T, screen):
+    """Tokens whose logits do not compare (NaN or infinite inputs) still get k different
+    experts below E and leave the other tokens' results alone, on expert counts that fill the
+    sixteen lanes and that do not."""
+    cfg = LayerConfig(f"tiled-nan-{E}", 256, E, k, 256, "bf16", "bf16", "fp8", "normal:0.5", [])
+    hl = W.host_layer(cfg, seed=520)
+    run = Run(cfg, hl, dev, max_tokens=T, screen_min_tokens=screen)
+    x = W.host_x(cfg, T, seed=520)
+    assert T * E > 6400
+    ids0, wts0, y0 = check_layer(run, x, label=f"{cfg.name} clean")
+    bad = [0, 17, 18, T - 1]
+    x[0] = 0x7FC0        # NaN
+    x[17, 3] = 0xFFC0    # one NaN, its sign bit set
+    x[18, 5] = 0x7F80    # +inf
+    x[T - 1, 7] = 0xFF80  # -inf
+    ids, wts, y = run.forward(x)
+    rids = run.route(x)[1]
+    ok = np.setdiff1d(np.arange(T), bad)
+    for i in (ids, rids):
+        assert np.array_equal(i[ok], ids0[ok]) and i.min() >= 0 and i.max() < E
+        assert all(len(set(i[t])) == k for t in bad)
+    assert np.array_equal(wts[ok], wts0[ok])
+    # an expert's tokens may fall into other columns, which changes no sum of a token
+    assert np.array_equal(y[ok], y0[ok])
+
+
+def test_tiled_routing_overflowing_logits(dev):
+    """Finite inputs whose logits overflow fp32 to -inf: the finite ones first, then the
+    infinite ones by index, none twice."""
+    cfg = LayerConfig("tiled-overflow", 512, 16, 4, 256, "bf16", "bf16", "fp8", None, [])
+    hl = W.host_layer(cfg, seed=521)
+    T = 405
+    run = Run(cfg, hl, dev, max_tokens=T, screen_min_tokens=-1)
+    x, w = np.zeros((T, cfg.hidden)), np.zeros((16, cfg.hidden))
+    x[:, 0] = 2.0 ** 100
+    x[:, 1] = 1.0
+    w[:, 0] = -(2.0 ** 100)
+    w[[3, 9], 0] = 0
+    w[[3, 9], 1] = 1.0, 2.0
+    hl.router_w[:] = _bf16(w)
+    run.rw = W.to_device(hl.router_w, dev)
+    _, ids, wts = run.route(_bf16(x))
+    assert np.all(ids == [9, 3, 0, 1])
+    e = np.exp(-1.0)
+    assert np.abs(wts - np.array([1 / (1 + e), e / (1 + e), 0, 0])).max() <= 1e-6
+
+
 def test_bitwise_repeatable_and_permutation_equivariant(dev):
     hl = W.host_layer(SMALL_FP8, seed=508)
     run = Run(SMALL_FP8, hl, dev, max_tokens=32)
