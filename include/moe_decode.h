@@ -129,7 +129,10 @@ typedef struct moe_decode_config {
                                 reach the top k get the exact logit (the selection is
                                 the same); needs bf16 x and router_w and H a multiple of
                                 256.  0 = library default (the smallest T with
-                                T*E*H >= 2^26 multiply-adds), negative = never */
+                                T*E*H >= 2^26 multiply-adds), negative = never.  Steps
+                                with T*E > 6400, E <= 256, topk <= 16 and H a multiple of
+                                256 never screen: a kernel that forms every logit in fp64
+                                on matrix cores is faster there */
     int32_t reserved[5];     /* must be zero */
 } moe_decode_config;
 
@@ -138,7 +141,8 @@ typedef struct moe_decode_stats {
     int32_t n_active;        /* experts with at least one token in the last forward */
     int32_t n_active_mfma;   /* of those, experts that ran on MFMA tiles */
     int32_t n_fallback;      /* router logits that needed the exact (double-double) path */
-    int32_t n_exact_logits;  /* router logits computed exactly (T*E unless screened) */
+    int32_t n_exact_logits;  /* router logits computed exactly: T*E, less those that the step
+                                left uncertain because they cannot reach the top k */
     int32_t route_screened;  /* 1 if the last forward screened the router logits */
     int64_t active_weight_bytes; /* unique expert weight + scale bytes the step streamed */
 } moe_decode_stats;

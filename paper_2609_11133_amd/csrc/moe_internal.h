@@ -61,7 +61,8 @@ constexpr int kWideChunk4 = 64;  // ... and NVFP4 weights
 // Screened routing by default from T*E*H >= 2^26 multiply-adds of exact logits: below
 // it the fixed costs of the extra pass outweigh the logits it saves.
 constexpr long kScreenMinMacs = 1L << 26;
-constexpr int kCandCounterOff = 32;  // int32 words from the fallback counter to the candidate counter
+constexpr int kCandCounterOff = 32;  // int32 words from the fallback counter to that of the screen's candidates
+                                     // (tiled routing: of the logits left uncertain)
 constexpr int kTicketOff = 48;       // ... and to the item counters of the large-batch kernels
 
 // K slices of the screened routing's partial sums: at most 16 and H/256, and the

@@ -540,7 +540,7 @@ struct RouteArgs {
     double2 *part;
     float *xmax, *wmax;
     int KS, Tmax;
-    int screened;  // the step counts as screened (statistics)
+    int screened;  // screen_kernel and route_cand_kernel run (with KS > 0; else route_tile_kernel)
 };
 
 // The 2-term FP8 split of one group of 32 inputs of token t (see fp8split.h).
@@ -654,7 +654,10 @@ __device__ __attribute__((always_inline)) inline void group_pairs(const RouteArg
     int nfb_total = 0, n_exact = A.T * E;
     if (threadIdx.x == 0) {  // in flight during the grouping; each counter is reset by its reader
         nfb_total = atomicExch(A.fb_acc, 0);
-        if (A.screened) n_exact = atomicExch(A.fb_acc + kCandCounterOff, 0);
+        if (A.KS) {  // screened: the logits computed exactly; tiled: the uncertain ones left out
+            const int n = atomicExch(A.fb_acc + kCandCounterOff, 0);
+            n_exact = A.screened ? n : n_exact - n;
+        }
     }
     for (int i = threadIdx.x; i < E * W; i += blockDim.x) mask[i] = 0u;
     __syncthreads();
@@ -1130,13 +1133,13 @@ __device__ inline int row_min(int v)
 }
 
 // The k largest logits of the token of each 16-lane row, ties to the lower expert: lane
-// j < k of the row gets choice j (its logit and expert), every lane the last choice's logit
-// and the number of unchosen experts tied with it.  Keys are the logits' ordered bits; 0
+// j < k of the row gets choice j (its logit and expert), every lane the last choice's
+// logit.  Keys are the logits' ordered bits; 0
 // stands for a chosen expert or none, below every logit's key, an infinity's and a NaN's
 // too, so the choices are k different experts below E whatever the logits are (k <= E).
 template <int V>
 __device__ __attribute__((always_inline)) inline void tile_topk(const float *l, int E, int k, int j, float &lj, int &ej,
-                                                                float &last, int &tied)
+                                                                float &last)
 {
     uint32_t key[V], m = 0u;
 #pragma unroll
@@ -1156,22 +1159,19 @@ __device__ __attribute__((always_inline)) inline void tile_topk(const float *l, 
         for (int v = 0; v < V; ++v) key[v] = 16 * v + j == e ? 0u : key[v];
     }
     last = from_ordered(m);
-    tied = 0;
-#pragma unroll
-    for (int v = 0; v < V; ++v) tied += key[v] == m ? 1 : 0;
 }
 
 __device__ __attribute__((always_inline)) inline void tile_topk_any(const float *l, int E, int k, int j, float &lj, int &ej,
-                                                                    float &last, int &tied)
+                                                                    float &last)
 {
     if (E <= 64)
-        tile_topk<4>(l, E, k, j, lj, ej, last, tied);
+        tile_topk<4>(l, E, k, j, lj, ej, last);
     else if (E <= 128)
-        tile_topk<8>(l, E, k, j, lj, ej, last, tied);
+        tile_topk<8>(l, E, k, j, lj, ej, last);
     else if (E <= 192)
-        tile_topk<12>(l, E, k, j, lj, ej, last, tied);
+        tile_topk<12>(l, E, k, j, lj, ej, last);
     else
-        tile_topk<16>(l, E, k, j, lj, ej, last, tied);
+        tile_topk<16>(l, E, k, j, lj, ej, last);
 }
 
 // The slices' sums of token t against experts r, r + 16, ...: done(e, sum, bound).  Up to 32
@@ -1352,9 +1352,9 @@ __global__ __launch_bounds__(256) void route_tile_kernel(RouteArgs A)
     }
     sync_wave();
     float lj, last;
-    int ej, tied;
+    int ej;
     for (int pass = 0;; ++pass) {
-        tile_topk_any(l, E, A.k, r, lj, ej, last, tied);
+        tile_topk_any(l, E, A.k, r, lj, ej, last);
         if (pass) break;
         const int nfb = __builtin_amdgcn_readfirstlane(s_nfb[wave]);
         int nex = 0;
@@ -1368,6 +1368,7 @@ __global__ __launch_bounds__(256) void route_tile_kernel(RouteArgs A)
             if (lane == 0) *lf = c + 0.0f;
             ++nex;
         }
+        if (lane == 0 && nex < nfb) atomicAdd(A.fb_acc + kCandCounterOff, nfb - nex);
         if (!nex) break;
         if (lane == 0) atomicAdd(A.fb_acc, nex);
         sync_wave();
@@ -1385,11 +1386,6 @@ __global__ __launch_bounds__(256) void route_tile_kernel(RouteArgs A)
         A.wts[o] = w;
         if (A.ids_user) A.ids_user[o] = ej;
         if (A.wts_user) A.wts_user[o] = w;
-    }
-    if (A.screened) {  // the experts that reach the top k: the choices and those tied with the last
-#pragma unroll
-        for (int o = 8; o >= 1; o >>= 1) tied += __shfl_xor(tied, o);
-        if (r == 0 && t < T) atomicAdd(A.fb_acc + kCandCounterOff, A.k + tied);
     }
     if (!A.do_group) return;
     wait_stores();
@@ -1473,8 +1469,9 @@ hipError_t launch_route(const Layer &L, const RouteParams &P, hipStream_t st)
     A.id_cache = lds + 2 * pairs <= 49152 ? 1 : 0;
     if (A.id_cache) lds += 2 * pairs;
     if (!P.do_group) lds = 0;
-    // Tiled routing above kTilePairs (token, expert) pairs, screened steps among them: up to
-    // 256 experts, 16 choices.  Four slices of the inputs while the tiles are
+    // Tiled routing above kTilePairs (token, expert) pairs, also where the screen was asked
+    // for: up to 256 experts, 16 choices, and H a multiple of 256 (ks_max > 0: the workspace
+    // holds no partial sums otherwise).  Four slices of the inputs while the tiles are
     // at most one per CU, fewer above (235B-shaped NVFP4 layer, step us with 1 / 2 / 4 / 8
     // slices: T=64 264 / 259 / 257 / 258, T=256 318 / 313 / 311 / 322; 480B-shaped T=1000
     // 1,768 / 1,767 / 1,783 / 1,804).
@@ -1483,7 +1480,6 @@ hipError_t launch_route(const Layer &L, const RouteParams &P, hipStream_t st)
         int ks = tt * et <= 256 ? 4 : (tt * et <= 512 ? 2 : 1);
         while (ks > 1 && (ks > P.ks_max || ks > L.H / 256)) ks /= 2;
         A.KS = ks;
-        A.screened = P.do_group && P.screen && L.act_bf16 && L.router_bf16 ? 1 : 0;
         const size_t lf = (size_t)2 * 16 * L.E * sizeof(float), bytes = lds > lf ? lds : lf;  // values, upper ends
         dim3 grid(ks, et, tt), block(256);
         if (L.act_bf16 && L.router_bf16)
