@@ -20,6 +20,7 @@
 #include "fp8split.h"
 #include "moe_internal.h"
 #include "own.h"
+#include "wave.h"
 
 namespace moe {
 namespace {
@@ -909,15 +910,14 @@ struct alignas(16) WideSeg {
 
 // K blocks per segment for NT token tiles.
 template <int NT>
-constexpr int kWideSegK = NT * 16 * 4 <= kWideArea ? 4 : (NT * 16 * 2 <= kWideArea ? 2 : 1);
+constexpr int kWideSegK = NT * 16 * 4 <= kWideArea ? 4 : 2;
 
 // Place of 16-byte piece p of token row t: the token XORed into the piece index so that
-// the 16 rows of a fragment read fall on 16 distinct bank groups (a 128-byte row holds
-// half of the banks, so there the token's low bit already picks the half).
+// the 16 rows of a fragment read fall on 16 distinct bank groups.
 template <int SEGK>
 __device__ inline int wide_place(int p, int t)
 {
-    return SEGK == 1 ? t * 128 + ((p ^ (t >> 1)) & 7) * 16 : t * (SEGK * 128) + ((p & ~15) | ((p ^ t) & 15)) * 16;
+    return t * (SEGK * 128) + ((p & ~15) | ((p ^ t) & 15)) * 16;
 }
 
 // One thread's share of staging a segment: a 16-byte piece of NT*SEGK/4 token rows in both
@@ -930,9 +930,8 @@ struct WideStager {
     static constexpr int kPieces = SEGK * 8;               // 16-byte pieces of a token row
     static constexpr int kRows = 64 * kWideW / kPieces;    // token rows per pass
     static constexpr int Q = 16 * NT / kRows;
-    static_assert(16 * NT % kRows == 0 && kRows % 8 == 0, "whole passes");
-    // rows kRows apart have the same swizzle
-    static constexpr bool kSame = kRows % 16 == 0;
+    static_assert(16 * NT <= kTok && 16 * NT % kRows == 0, "a segment holds the tiles, in whole passes");
+    static_assert(kRows % 16 == 0, "rows kRows apart have the same swizzle");
     uint32_t voff[Q], eoff;
     int tid, so;
     u32x4v code[2][Q];
@@ -969,7 +968,7 @@ struct WideStager {
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int q = 0; q < Q; ++q)
-                *reinterpret_cast<u32x4v *>(&S.code[h][0] + (kSame ? so + kRows * q * (SEGK * 128) : wide_place<SEGK>(tid & (kPieces - 1), kRows * q + tid / kPieces))) = code[h][q];
+                *reinterpret_cast<u32x4v *>(&S.code[h][0] + so + kRows * q * (SEGK * 128)) = code[h][q];
         reinterpret_cast<uint32_t *>(&S.ex[0][0])[tid] = ex;
     }
 };
@@ -1195,14 +1194,6 @@ __device__ inline void w13_item_wide(WideRing &R, const WideTiles &W, const Wide
     }
 }
 
-// A chunk record, the same for every lane, in scalar registers.
-__device__ inline int4 wide_rec(const int4 *recs, int i)
-{
-    const int4 r = recs[i];
-    return make_int4(__builtin_amdgcn_readfirstlane(r.x), __builtin_amdgcn_readfirstlane(r.y),
-                     __builtin_amdgcn_readfirstlane(r.z), 0);
-}
-
 // Calls go(integral_constant NT) with the token tiles of a chunk of mc tokens.
 template <class F>
 __device__ inline void wide_tiles_of(int mc, F go)
@@ -1234,7 +1225,7 @@ __global__ __launch_bounds__(64 * kWideW) __attribute__((amdgpu_waves_per_eu(2))
     const int n_items = meta[mi.n_mfma_chunks()] * tiles;
     int item = blockIdx.x, nxt = item + gridDim.x;
     if (item >= n_items) return;  // uniform over the workgroup
-    int4 rec = wide_rec(recs, item / tiles);  // {expert, first slot, tokens, -}
+    int4 rec = chunk_record(recs, item / tiles);  // {expert, first slot, tokens, -}
     WideTiles W, N;
     w13_wide_tiles<PK>(W, ew + (size_t)rec.x * ewb, es + (size_t)rec.x * esb, H, I, row0(item), lane);
     WideRing R;
@@ -1245,7 +1236,7 @@ __global__ __launch_bounds__(64 * kWideW) __attribute__((amdgpu_waves_per_eu(2))
         const int after = tid == 0 ? atomicAdd(ticket, 1) + 2 * (int)gridDim.x : 0;
         const bool more = nxt < n_items;
         const int ni = more ? nxt : item;  // after the last item: its own blocks again
-        const int4 nrec = wide_rec(recs, ni / tiles);
+        const int4 nrec = chunk_record(recs, ni / tiles);
         const int ntok = tid < nrec.z && tid < kWideChunk ? tok_of[nrec.y + tid] : 0;
         w13_wide_tiles<PK>(N, ew + (size_t)nrec.x * ewb, es + (size_t)nrec.x * esb, H, I, row0(ni), lane);
         wide_tiles_of(rec.z, [&](auto nt) {
@@ -1297,7 +1288,7 @@ __global__ __launch_bounds__(64 * kWideW) __attribute__((amdgpu_waves_per_eu(2))
     const int n_items = meta[mi.n_mfma_chunks()] * tiles;
     int item = blockIdx.x, nxt = item + gridDim.x;
     if (item >= n_items) return;  // uniform over the workgroup
-    int4 rec = wide_rec(recs, item / tiles);
+    int4 rec = chunk_record(recs, item / tiles);
     WideTiles W, N;
     w2_wide_tiles<PK>(W, ew + (size_t)rec.x * ewb, es + (size_t)rec.x * esb, H, I, row0(item), lane);
     WideRing R;
@@ -1306,7 +1297,7 @@ __global__ __launch_bounds__(64 * kWideW) __attribute__((amdgpu_waves_per_eu(2))
         const int after = tid == 0 ? atomicAdd(ticket, 1) + 2 * (int)gridDim.x : 0;
         const bool more = nxt < n_items;
         const int ni = more ? nxt : item;  // after the last item: its own blocks again
-        const int4 nrec = wide_rec(recs, ni / tiles);
+        const int4 nrec = chunk_record(recs, ni / tiles);
         w2_wide_tiles<PK>(N, ew + (size_t)nrec.x * ewb, es + (size_t)nrec.x * esb, H, I, row0(ni), lane);
         wide_tiles_of(rec.z, [&](auto nt) {
             constexpr int NT = decltype(nt)::value;
@@ -1497,8 +1488,7 @@ int mfma_grid(const Layer &L, int T, int k, int items_per_chunk, int per_block)
 {
     const long pairs = (long)T * k;
     const long recs = pairs < L.E ? pairs : L.E;
-    const int chunk = chunk_tokens(L, T, k);
-    const long chunks = recs + (pairs + chunk - 1) / chunk;  // >= number of chunk records
+    const long chunks = recs + (pairs + kMfmaChunk - 1) / kMfmaChunk;  // >= number of chunk records
     const long blocks = (chunks * items_per_chunk + per_block - 1) / per_block;
     return blocks < 1 ? 1 : (blocks > 65535 ? 65535 : (int)blocks);
 }

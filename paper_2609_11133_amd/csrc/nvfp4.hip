@@ -49,6 +49,7 @@
 
 #include "moe_internal.h"
 #include "own.h"
+#include "wave.h"
 
 namespace moe {
 namespace {
@@ -724,14 +725,6 @@ __device__ inline void w_tiles_of(int mc, F go)
     else go(std::integral_constant<int, 2>{});
 }
 
-// A chunk record, the same for every lane, in scalar registers.
-__device__ inline int4 w_rec(const int4 *recs, int i)
-{
-    const int4 r = recs[i];
-    return make_int4(__builtin_amdgcn_readfirstlane(r.x), __builtin_amdgcn_readfirstlane(r.y),
-                     __builtin_amdgcn_readfirstlane(r.z), 0);
-}
-
 // gate/up: item = (chunk, 16 * kWW rows of the intermediate dimension); wave w streams the
 // gate and the up rows i0 + 16w .. +16.
 template <bool PK, bool GS>
@@ -762,7 +755,7 @@ __global__ __launch_bounds__(64 * kWW) __attribute__((amdgpu_waves_per_eu(2))) v
             W.srow[a] = se + (size_t)row * (H / 16);
         }
     };
-    int4 rec = w_rec(recs, item / tiles);  // {expert, first slot, tokens, -}
+    int4 rec = chunk_record(recs, item / tiles);  // {expert, first slot, tokens, -}
     WTiles W, N;
     tiles_of(W, rec.x, row0(item));
     WRing R;
@@ -773,7 +766,7 @@ __global__ __launch_bounds__(64 * kWW) __attribute__((amdgpu_waves_per_eu(2))) v
         const int after = tid == 0 ? atomicAdd(ticket, 1) + 2 * (int)gridDim.x : 0;
         const bool more = nxt < n_items;
         const int ni = more ? nxt : item;  // after the last item: its own blocks again
-        const int4 nrec = w_rec(recs, ni / tiles);
+        const int4 nrec = chunk_record(recs, ni / tiles);
         const int ntok = tid < nrec.z && tid < kWideChunk4 ? tok_of[nrec.y + tid] : 0;
         tiles_of(N, nrec.x, row0(ni));
         w_tiles_of(rec.z, [&](auto nt) {
@@ -841,7 +834,7 @@ __global__ __launch_bounds__(64 * kWW) __attribute__((amdgpu_waves_per_eu(2))) v
             W.srow[a] = se + (size_t)row * (I / 16);
         }
     };
-    int4 rec = w_rec(recs, item / tiles);
+    int4 rec = chunk_record(recs, item / tiles);
     WTiles W, N;
     tiles_of(W, rec.x, row0(item));
     WRing R;
@@ -850,7 +843,7 @@ __global__ __launch_bounds__(64 * kWW) __attribute__((amdgpu_waves_per_eu(2))) v
         const int after = tid == 0 ? atomicAdd(ticket, 1) + 2 * (int)gridDim.x : 0;
         const bool more = nxt < n_items;
         const int ni = more ? nxt : item;  // after the last item: its own blocks again
-        const int4 nrec = w_rec(recs, ni / tiles);
+        const int4 nrec = chunk_record(recs, ni / tiles);
         tiles_of(N, nrec.x, row0(ni));
         w_tiles_of(rec.z, [&](auto nt) {
             constexpr int NT = decltype(nt)::value;

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "moe_internal.h"
+#include "wave.h"
 
 namespace moe {
 
@@ -30,21 +31,6 @@ struct OwnLds {
     static size_t bytes(int E, int P, int tok) { return sizeof(float) * (18 * (size_t)P + (P < E ? P : E) + (P + tok - 1) / tok + 1); }
 };
 
-// Inclusive prefix sum over the wave with DPP row shifts, then the row totals; returns the
-// wave's total.
-__device__ inline int own_scan(int &v, int lane)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
-    const int t0 = __builtin_amdgcn_readlane(v, 15), t1 = __builtin_amdgcn_readlane(v, 31),
-              t2 = __builtin_amdgcn_readlane(v, 47), t3 = __builtin_amdgcn_readlane(v, 63);
-    const int row = lane >> 4;
-    v += (row >= 1 ? t0 : 0) + (row >= 2 ? t1 : 0) + (row >= 3 ? t2 : 0);
-    return t0 + t1 + t2 + t3;
-}
-
 // The step's passes in expert order (wave 0) and the combine's slots and weights (the other
 // waves), into LDS; returns the number of passes after a barrier.
 template <int TOK, int W>
@@ -65,7 +51,7 @@ __device__ inline int own_passes(const OwnLds &S, int *s_np, const int32_t *__re
         for (int u = 0; u < kOwnChunks / 64; ++u) {
             const int cnt = 64 * u + lane < n ? (rc[u].z + TOK - 1) / TOK : 0;
             int inc = cnt;
-            const int tot = own_scan(inc, lane);
+            const int tot = wave_inclusive_scan(inc, lane);
             for (int c = 0; c < cnt; ++c)
                 S.pass[before + inc - cnt + c] =
                     (uint32_t)rc[u].x | (uint32_t)min(TOK, rc[u].z - TOK * c) << 10 | (uint32_t)(rc[u].y + TOK * c) << 16;

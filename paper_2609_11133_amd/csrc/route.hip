@@ -9,6 +9,7 @@
 
 #include "fp8split.h"
 #include "moe_internal.h"
+#include "wave.h"
 
 namespace moe {
 namespace {
@@ -360,21 +361,6 @@ __device__ inline void load32_f32<float>(const float *p, float (&v)[32])
 }
 
 // ------------------------------------------------------------------ block scan
-
-// Inclusive prefix sum over a wave with DPP row shifts (each 16-lane row), then the
-// row totals read from lanes 15, 31, 47 and 63.  Returns the wave total.
-__device__ inline int wave_inclusive_scan(int &v, int lane)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
-    const int t0 = __builtin_amdgcn_readlane(v, 15), t1 = __builtin_amdgcn_readlane(v, 31),
-              t2 = __builtin_amdgcn_readlane(v, 47), t3 = __builtin_amdgcn_readlane(v, 63);
-    const int row = lane >> 4;
-    v += (row >= 1 ? t0 : 0) + (row >= 2 ? t1 : 0) + (row >= 3 ? t2 : 0);
-    return t0 + t1 + t2 + t3;
-}
 
 // Exclusive prefix sums of four counters over the 256 threads of a workgroup.
 __device__ inline void block_exscan4(int (&v)[4], int (&tot)[4], int *sh /* [4 waves][4] */)
