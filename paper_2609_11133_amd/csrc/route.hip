@@ -15,6 +15,7 @@ namespace moe {
 namespace {
 
 constexpr int kWave = 64;
+constexpr int kThreads = 256;  // threads per workgroup of every routing kernel
 
 // Values exchanged between workgroups of this kernel (logits, selected experts) are
 // written and read with device-scope atomic stores and loads, which bypass the
@@ -504,6 +505,9 @@ __device__ __attribute__((always_inline)) inline void token_topk(const float *__
 // start of every launch.
 
 
+// No kernel reads more than this (256 bytes: four lines of argument memory, each a round
+// trip to the host's memory when first touched): workgroup and grid sizes are constants or
+// follow from it, since the dispatch's own would lie in a fifth line.
 struct RouteArgs {
     const void *x;
     const void *wr;
@@ -528,6 +532,7 @@ struct RouteArgs {
     int KS, Tmax;
     int screened;  // screen_kernel and route_cand_kernel run (with KS > 0; else route_tile_kernel)
 };
+static_assert(sizeof(RouteArgs) <= 256);
 
 // The 2-term FP8 split of one group of 32 inputs of token t (see fp8split.h).
 template <typename XT>
@@ -645,21 +650,21 @@ __device__ __attribute__((always_inline)) inline void group_pairs(const RouteArg
             n_exact = A.screened ? n : n_exact - n;
         }
     }
-    for (int i = threadIdx.x; i < E * W; i += blockDim.x) mask[i] = 0u;
+    for (int i = threadIdx.x; i < E * W; i += kThreads) mask[i] = 0u;
     __syncthreads();
     // this thread's choices, eight loads in flight at a time (small loops: at small batches
     // this code is fetched cold, and 32 unrolled steps took 1.5 us longer)
     auto token = [&](int p) { return k == 1 ? p : (int)__umulhi((uint32_t)p, A.rk); };  // p / k
-    for (int p0 = threadIdx.x; p0 < P; p0 += 8 * blockDim.x) {
+    for (int p0 = threadIdx.x; p0 < P; p0 += 8 * kThreads) {
         int e8[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int p = p0 + u * blockDim.x;
+            const int p = p0 + u * kThreads;
             e8[u] = p < P ? ld_dev(&A.ids[p]) : 0;
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int p = p0 + u * blockDim.x;
+            const int p = p0 + u * kThreads;
             if (p < P) {
                 const int tt = token(p);
                 atomicOr(&mask[e8[u] * W + tt / 32], 1u << (tt % 32));
@@ -728,7 +733,7 @@ __device__ __attribute__((always_inline)) inline void group_pairs(const RouteArg
         if (A.chunk != kMfmaChunk) A.fb_acc[kTicketOff] = A.fb_acc[kTicketOff + 1] = 0;
     }
     __syncthreads();
-    for (int p = threadIdx.x; p < P; p += blockDim.x) {
+    for (int p = threadIdx.x; p < P; p += kThreads) {
         const int tt = token(p), e = cached ? idc[p] : ld_dev(&A.ids[p]);
         int rank = __popc(mask[e * W + tt / 32] & ((1u << (tt % 32)) - 1u));
         if (A.prefix)
@@ -788,7 +793,7 @@ __global__ __launch_bounds__(256) void route_kernel(RouteArgs A)
                    A.ids_user ? A.ids_user + (size_t)t * A.k : nullptr,
                    A.wts_user ? A.wts_user + (size_t)t * A.k : nullptr, lane);
     } else if (A.xs_hi) {
-        write_split<XT>(A, xr, t, threadIdx.x - kWave, blockDim.x - kWave);
+        write_split<XT>(A, xr, t, threadIdx.x - kWave, kThreads - kWave);
     } else if constexpr (sizeof(XT) == 2) {
         if (A.x16) write_x16(A, xr, t, wave - 1, 3, lane);
     }
@@ -986,7 +991,7 @@ __global__ __launch_bounds__(256) void route_cand_kernel(RouteArgs A)
 #pragma unroll
     for (int s2 = 0; s2 < kMaxKS; ++s2) mxt = fmaxf(mxt, xm[s2]);
     const double u = 0x1p-23, g = kScreenChunk * u / (1.0 - kScreenChunk * u);
-    for (int e = threadIdx.x; e < E; e += blockDim.x) {
+    for (int e = threadIdx.x; e < E; e += kThreads) {
         double2 d[kMaxKS];
         float wm[kMaxKS];
 #pragma unroll
@@ -1010,7 +1015,7 @@ __global__ __launch_bounds__(256) void route_cand_kernel(RouteArgs A)
         s_lo[e] = f32_down(Sb - D);
         s_hi[e] = f32_up(Sb + D);
     }
-    for (int i = threadIdx.x; i < kMaxE / 32; i += blockDim.x) s_cand[i] = 0u;
+    for (int i = threadIdx.x; i < kMaxE / 32; i += kThreads) s_cand[i] = 0u;
     __syncthreads();
 
     // 2. wave 0: LB = k-th largest lower bound, the candidates hi >= LB in expert
@@ -1038,7 +1043,7 @@ __global__ __launch_bounds__(256) void route_cand_kernel(RouteArgs A)
             atomicAdd(A.fb_acc + kCandCounterOff, n);
         }
     } else if (A.xs_hi) {
-        write_split<uint16_t>(A, xr, t, threadIdx.x - kWave, blockDim.x - kWave);
+        write_split<uint16_t>(A, xr, t, threadIdx.x - kWave, kThreads - kWave);
     } else if (A.x16) {
         write_x16(A, xr, t, wave - 1, 3, lane);
     }
@@ -1281,7 +1286,7 @@ __global__ __launch_bounds__(256) void route_tile_kernel(RouteArgs A)
     }
     wait_stores();
     __syncthreads();
-    const int nwg = gridDim.x * gridDim.y;
+    const int nwg = KS * ((E + 15) / 16), ntt = (T + 15) / 16;  // workgroups of a token tile, token tiles
     if (tid == 0) s_flag = atomicAdd(&A.cnt_tok[blockIdx.z * kCounterStride], 1);
     __syncthreads();
     const int wg = s_flag;  // order of arrival in the token tile
@@ -1376,8 +1381,8 @@ __global__ __launch_bounds__(256) void route_tile_kernel(RouteArgs A)
     if (!A.do_group) return;
     wait_stores();
     __syncthreads();
-    if (gridDim.z > 1) {
-        if (tid == 0) s_flag = atomicAdd(A.cnt_all, 1) == (int)gridDim.z - 1;
+    if (ntt > 1) {
+        if (tid == 0) s_flag = atomicAdd(A.cnt_all, 1) == ntt - 1;
         __syncthreads();
         if (!s_flag) return;
     }
