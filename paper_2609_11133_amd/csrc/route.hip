@@ -111,6 +111,21 @@ __device__ inline void load8<float>(const float *p, double (&v)[8])
     v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
+// The lanes' double-double sums and the bias b, added and rounded.
+__device__ __attribute__((always_inline)) inline float wave_dd_to_f32(double hi, double lo, double b)
+{
+    double nh = hi + lo;  // normalise the lane's pair before combining
+    lo = lo - (nh - hi);
+    hi = nh;
+#pragma unroll
+    for (int o = kWave / 2; o >= 1; o >>= 1) {
+        double h2 = __shfl_xor(hi, o), l2 = __shfl_xor(lo, o);
+        dd_add(hi, lo, h2, l2);
+    }
+    dd_add(hi, lo, b, 0.0);
+    return round_dd_to_f32(hi, lo);
+}
+
 // Exact (double-double) logit of one (token, expert) pair, computed by one wave: the
 // slow path taken when the fp64 sum cannot certify its fp32 rounding.
 template <typename XT, typename WT>
@@ -130,16 +145,7 @@ __device__ __attribute__((always_inline)) inline float wave_logit_exact(const XT
             lo += ee;
         }
     }
-    double nh = hi + lo;  // normalise the lane's pair before combining
-    lo = lo - (nh - hi);
-    hi = nh;
-#pragma unroll
-    for (int o = kWave / 2; o >= 1; o >>= 1) {
-        double h2 = __shfl_xor(hi, o), l2 = __shfl_xor(lo, o);
-        dd_add(hi, lo, h2, l2);
-    }
-    dd_add(hi, lo, b, 0.0);
-    return round_dd_to_f32(hi, lo);
+    return wave_dd_to_f32(hi, lo, b);
 }
 
 // Eight consecutive inputs of one lane, as raw bits (bf16: 4 words, fp32: 8 words).
@@ -168,6 +174,39 @@ __device__ inline double elem(const Chunk8<T> &c, int i)
         return (double)__uint_as_float((i & 1) ? (c.d[i >> 1] & 0xFFFF0000u) : (c.d[i >> 1] << 16));
     else
         return (double)__uint_as_float(c.d[i]);
+}
+
+// wave_logit_exact with up to 4096 inputs of each row in flight at a time: where one wave's
+// recomputation ends the step, the round trips are what it costs.  Routing stage with this,
+// the bound without its slack and the biases loaded with the sums, us (96 experts of 3072
+// inputs, Zipf-skewed): T=256 25.9 -> 24.8, T=512 36.5 -> 35.0.
+template <typename XT, typename WT>
+__device__ __attribute__((always_inline)) inline float wave_logit_exact_ahead(const XT *__restrict__ xr, const WT *__restrict__ wrow,
+                                                                              double b, int H, int lane)
+{
+    constexpr int SEG = sizeof(XT) == 2 && sizeof(WT) == 2 ? 8 : 4;  // chunks of 512 inputs
+    double hi = 0.0, lo = 0.0;
+    for (int h0 = lane * 8; h0 < H; h0 += 512 * SEG) {
+        Chunk8<XT> xc[SEG];
+        Chunk8<WT> wc[SEG];
+#pragma unroll
+        for (int j = 0; j < SEG; ++j) {
+            const int h = h0 + 512 * j < H ? h0 + 512 * j : h0;  // past the row: the first chunk again, not added
+            ld_chunk<XT>(xr + h, xc[j]);
+            ld_chunk<WT>(wrow + h, wc[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < SEG; ++j)
+            if (h0 + 512 * j < H)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    double ss, ee;
+                    two_sum(hi, elem<XT>(xc[j], i) * elem<WT>(wc[j], i), ss, ee);  // exact product
+                    hi = ss;
+                    lo += ee;
+                }
+    }
+    return wave_dd_to_f32(hi, lo, b);
 }
 
 constexpr int kEPW = 4;  // experts per wave, at most
@@ -1165,7 +1204,7 @@ __device__ __attribute__((always_inline)) inline void tile_topk_any(const float 
         tile_topk<16>(l, E, k, j, lj, ej, last);
 }
 
-// The slices' sums of token t against experts r, r + 16, ...: done(e, sum, bound).  Up to 32
+// The slices' sums of token t against experts r, r + 16, ...: done(e, sum, bound, bias).  Up to 32
 // 16-byte loads are in flight at a time, past the per-XCD L2 (the producers' stores went
 // past theirs); one expert's at a time cost a memory round trip each.
 template <int KS, class F>
@@ -1176,6 +1215,9 @@ __device__ __attribute__((always_inline)) inline void tile_sums(const RouteArgs 
     const __amdgpu_buffer_rsrc_t pr = screen_rsrc(A.part, (uint32_t)KS * A.Tmax * E * 16u);
     for (int e0 = r; e0 < E; e0 += 16 * VG) {
         u32x4v u[VG][KS];
+        float bias[VG];  // in flight with the sums
+#pragma unroll
+        for (int v = 0; v < VG; ++v) bias[v] = A.bias && e0 + 16 * v < E ? A.bias[e0 + 16 * v] : 0.f;
 #pragma unroll
         for (int v = 0; v < VG; ++v)
 #pragma unroll
@@ -1192,7 +1234,7 @@ __device__ __attribute__((always_inline)) inline void tile_sums(const RouteArgs 
                     S += __longlong_as_double((long long)(((uint64_t)u[v][q][1] << 32) | u[v][q][0]));
                     B += __longlong_as_double((long long)(((uint64_t)u[v][q][3] << 32) | u[v][q][2]));
                 }
-                done(e0 + 16 * v, S, B);
+                done(e0 + 16 * v, S, B, (double)bias[v]);
             }
     }
 }
@@ -1204,6 +1246,7 @@ __global__ __launch_bounds__(256) void route_tile_kernel(RouteArgs A)
     __shared__ double s_red[4][256];  // the waves' sums; then the list of uncertain logits (16 bits each)
     __shared__ double s_nx[4][16], s_nw[4][16];
     __shared__ int s_flag, s_nfb[4];
+    __shared__ int s_width[16];
     __shared__ int s_scan[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, g = lane >> 4;
@@ -1311,26 +1354,29 @@ __global__ __launch_bounds__(256) void route_tile_kernel(RouteArgs A)
     // top k.  A logit that the bound does not certify goes in at the lower end of its
     // interval, so the k-th largest value is a lower bound of the k-th largest logit, and the
     // logit matters only if its upper end reaches that value (ends equal to it may tie).
-    // Under cancellation the two ends are many fp32 steps apart.  Those that matter are
-    // recomputed exactly (every one where the logits are asked for) and the top k taken
-    // again, all within the wave; the others stay below the k largest.
+    // Under cancellation the two ends are many fp32 steps apart; s_width holds the token's
+    // largest distance of them, rounded up, as float bits (ordered like the floats, a NaN
+    // above all).  The logits that matter are recomputed exactly (every one where the logits
+    // are asked for) and the top k taken again, all within the wave; the others stay below
+    // the k largest.
     const int tk = 4 * wave + g, t = t0 + tk;
     float *l = (float *)lds + (size_t)tk * E;  // this row's logits
-    float *lu = l + 16 * (size_t)E;            // ... and the upper ends of the uncertain ones
     uint16_t *fb = (uint16_t *)&s_red[wave][0];  // the wave's uncertain logits
     if (lane == 0) s_nfb[wave] = 0;
+    if (r == 0) s_width[tk] = 0;
     if (tid == 0) st_dev(&A.cnt_tok[blockIdx.z * kCounterStride], 0);
     {
         // one accumulator's roundings (its MFMAs, four products each), the accumulators', the
         // waves' and the slices' additions and the bias; twice the recursive-summation bound
-        const int D = 4 * ((per + 2 * B) * 8 / kTileAcc) + 4 + 4 + KS + 1 + 2;
+        // (the zeros that a slice's last batch is filled with are added without rounding)
+        const int D = 4 * (per * 8 / kTileAcc) + 4 + 4 + KS + 1 + 2;
         const double gamma = (double)D * 0x1p-52;
-        auto done = [&](int e, double S, double Bd) {
-            const double bias = A.bias ? (double)A.bias[e] : 0.0;
+        auto done = [&](int e, double S, double Bd, double bias) {
             float c, up;
             if (!certain_f32(S + bias, gamma * (Bd + fabs(bias)), c, up)) {
                 fb[atomicAdd(&s_nfb[wave], 1)] = (uint16_t)(g * kTileE + e);
-                lu[e] = up;
+                const float wd = (float)((double)up - (double)c);
+                atomicMax(&s_width[tk], (int)(__float_as_uint(nextafterf(wd, INFINITY)) & 0x7FFFFFFFu));
             }
             l[e] = c + 0.0f;  // -0 -> +0
         };
@@ -1353,8 +1399,9 @@ __global__ __launch_bounds__(256) void route_tile_kernel(RouteArgs A)
             const int fg = __builtin_amdgcn_readfirstlane((int)fb[i] / kTileE);
             const int e = __builtin_amdgcn_readfirstlane((int)fb[i] % kTileE);
             float *lf = (float *)lds + (size_t)(4 * wave + fg) * E + e;
-            if (A.do_group && lf[16 * (size_t)E] < __shfl(last, 16 * fg)) continue;
-            const float c = wave_logit_exact<XT, WT>(x + (size_t)(t0 + 4 * wave + fg) * H, (const WT *)A.wr + (size_t)e * H,
+            const float up = (float)((double)*lf + (double)__int_as_float(s_width[4 * wave + fg]));
+            if (A.do_group && up < __shfl(last, 16 * fg)) continue;
+            const float c = wave_logit_exact_ahead<XT, WT>(x + (size_t)(t0 + 4 * wave + fg) * H, (const WT *)A.wr + (size_t)e * H,
                                                      A.bias ? (double)A.bias[e] : 0.0, H, lane);
             if (lane == 0) *lf = c + 0.0f;
             ++nex;
@@ -1471,7 +1518,7 @@ hipError_t launch_route(const Layer &L, const RouteParams &P, hipStream_t st)
         int ks = tt * et <= 256 ? 4 : (tt * et <= 512 ? 2 : 1);
         while (ks > 1 && (ks > P.ks_max || ks > L.H / 256)) ks /= 2;
         A.KS = ks;
-        const size_t lf = (size_t)2 * 16 * L.E * sizeof(float), bytes = lds > lf ? lds : lf;  // values, upper ends
+        const size_t lf = (size_t)16 * L.E * sizeof(float), bytes = lds > lf ? lds : lf;
         dim3 grid(ks, et, tt), block(256);
         if (L.act_bf16 && L.router_bf16)
             route_tile_kernel<uint16_t, uint16_t><<<grid, block, bytes, st>>>(A);
