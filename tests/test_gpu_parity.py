@@ -676,15 +676,23 @@ WIDE_FP8 = [LayerConfig("wide-k6-5", 768, 8, 2, 640, "bf16", "bf16", "fp8", "zip
             LayerConfig("wide-k4-3", 512, 8, 2, 384, "f32", "bf16", "fp8", "zipf:1.1", [])]
 
 
+def _items(cfg):
+    """Work items of the wide kernels with one chunk per expert."""
+    return cfg.n_experts * (cfg.inter // 128 + cfg.hidden // 256)
+
+
 @pytest.mark.parametrize("cfg", WIDE_FP8, ids=lambda c: c.name)
 @pytest.mark.parametrize("layout", [0, 1], ids=["rows", "packed"])
 def test_wide_chunks(dev, cfg, layout):
     """FP8 layers on both sides of the switch to 128-token chunks (T*k*I above 20,000 per
-    expert packed, 26,000 row-major).  The Zipf-skewed batches give chunks of few tokens, of
-    every number of token-tile pairs (2, 4, 6, 8 tiles) and, at the largest, several chunks
-    of one expert."""
+    expert packed, 26,000 row-major, and 64 pairs per expert on layers of few items).  The
+    Zipf-skewed batches give chunks of few tokens, of every number of token-tile pairs (2, 4,
+    6, 8 tiles) and, at the largest, several chunks of one expert."""
     hl = W.host_layer(cfg, seed=611)
-    edge = (26000 if layout == 0 else 20000) * cfg.n_experts // (cfg.topk * cfg.inter)
+    per = 26000 if layout == 0 else 20000
+    edge = max(per * cfg.n_experts // (cfg.topk * cfg.inter),
+               64 * cfg.n_experts // cfg.topk - 1)
+    assert _items(cfg) < 448
     run = Run(cfg, hl, dev, max_tokens=700, weight_layout=layout)
     sizes = set()
     for T in (edge, edge + 1, 340, 700):
@@ -711,10 +719,12 @@ WIDE_NV = [LayerConfig("nv-wide-k5-3", 1280, 8, 2, 768, "bf16", "bf16", "nvfp4",
 @pytest.mark.parametrize("layout", [0, 1], ids=["rows", "packed"])
 def test_nvfp4_wide_chunks(dev, cfg, layout):
     """NVFP4 layers on both sides of the switch to 64-token chunks (more than 13 pairs and
-    T*k*I above 13,000 per expert packed, 3 and 7,000 row-major); the Zipf-skewed batches
-    give chunks of both token-tile counts and several chunks of one expert."""
+    T*k*I above 13,000 per expert packed, 3 and 7,000 row-major; on these layers of few items
+    from 48 and 40 pairs); the Zipf-skewed batches give chunks of both token-tile counts and
+    several chunks of one expert."""
     hl = W.host_layer(cfg, seed=621)
-    per = max(13, 13000 // cfg.inter) if layout else max(3, 7000 // cfg.inter)
+    assert _items(cfg) < 448
+    per = max(13, 13000 // cfg.inter, 47) if layout else max(3, 7000 // cfg.inter, 39)
     edge = per * cfg.n_experts // cfg.topk
     run = Run(cfg, hl, dev, max_tokens=300, weight_layout=layout)
     sizes = set()
