@@ -129,10 +129,11 @@ typedef struct moe_decode_config {
                                 reach the top k get the exact logit (the selection is
                                 the same); needs bf16 x and router_w and H a multiple of
                                 256.  0 = library default (the smallest T with
-                                T*E*H >= 2^26 multiply-adds), negative = never.  Steps
-                                with T*E > 6400, E <= 256, topk <= 16 and H a multiple of
-                                256 never screen: a kernel that forms every logit in fp64
-                                on matrix cores is faster there */
+                                T*E*H >= 2^26 multiply-adds), negative = never.  Large
+                                steps with E <= 256, topk <= 16 and H a multiple of 256
+                                (from T = 50 where H >= 3072, 128 or 256 below) do not
+                                screen: a kernel that forms every logit in fp64 on matrix
+                                cores is faster there */
     int32_t reserved[5];     /* must be zero */
 } moe_decode_config;
 

@@ -1134,11 +1134,27 @@ __global__ __launch_bounds__(256) void route_cand_kernel(RouteArgs A)
 constexpr int kTileE = 256;  // experts at most (16 keys per lane)
 constexpr int kTileK = 16;   // choices at most (one per lane of a row)
 constexpr int kTileAcc = 4;  // accumulators per wave
-// Below, the fixed phases (the slices' hand-off, a token tile's top-k in one workgroup) cost
-// more than the logits save.  Step us, route_kernel / tiled: 235B-shaped T=24 (3,072 pairs)
-// 208 / 211, T=48 246 / 244, T=64 258 / 257; 480B-shaped T=64 956 / 951; 160 experts T=40
-// (6,400) 281 / 280, T=64 324 / 320; 32 experts T=64 26.9 / 30.3.
-constexpr long kTilePairs = 6400;
+
+// Where the tiled routing runs.  Its fixed phases (the slices' hand-off, a token tile's top-k
+// in one workgroup, longer with more experts) cost more than the logits save on few (token,
+// expert) pairs, and with bf16 inputs on short ones, whose products route_kernel forms in fp32.
+// Step us against the other kernels (route_kernel, from 2^26 multiply-adds the screen),
+// without a router bias / Zipf-skewed:
+//   H 4096  128 experts T=51 +0.5 / +0.1, T=59 -2.0 / +1.3; 160 T=41 +0.7 / +3.7, T=54 -1.6 /
+//           +1.5, T=75 -2.5 / +1.2; 256 T=34 -1.2 / +3.7, T=55 -4.8 / -0.9, T=129 -13 / -7.2
+//   H 2048  64 experts T=102 +1.4 / +2.4, T=157 -1.4 / +1.4, T=219 -3.5 / -3.0; 128 T=94
+//           +1.1 / +2.9, T=129 -2.3 / -0.5; 160 T=104 +1.0 / +1.6, T=157 -1.4 / -0.8; 256
+//           T=129 +1.1 / +4.0, T=188 +2.7 / +7.2, T=258 -7.2 / -3.3
+//   H 1024  32 experts T=204 +1.3 / +2.3, T=313 -0.5 / -0.6; 64 T=133 +1.3 / +1.6, T=219 -2.7 /
+//           -2.8; 128 T=94 +2.1 / +4.4, T=129 -0.5 / 0.0; 256 T=65 +3.2 / +4.6, T=129 -2.8 / -3.4
+bool tile_routes(const Layer &L, const RouteParams &P)
+{
+    const long pairs = (long)P.T * L.E;
+    if (L.E > kTileE || P.k > kTileK || P.ks_max == 0 || pairs <= 6400) return false;
+    if (!L.act_bf16 || !L.router_bf16) return true;
+    if (L.H >= 3072) return P.T >= 50;
+    return pairs >= 10000 && P.T >= (L.E > 192 && L.H >= 2048 ? 256 : 128);
+}
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
@@ -1507,13 +1523,12 @@ hipError_t launch_route(const Layer &L, const RouteParams &P, hipStream_t st)
     A.id_cache = lds + 2 * pairs <= 49152 ? 1 : 0;
     if (A.id_cache) lds += 2 * pairs;
     if (!P.do_group) lds = 0;
-    // Tiled routing above kTilePairs (token, expert) pairs, also where the screen was asked
-    // for: up to 256 experts, 16 choices, and H a multiple of 256 (ks_max > 0: the workspace
-    // holds no partial sums otherwise).  Four slices of the inputs while the tiles are
+    // Tiled routing, also where the screen was asked for; it needs H a multiple of 256 (ks_max
+    // > 0: the workspace holds no partial sums otherwise).  Four slices of the inputs while the tiles are
     // at most one per CU, fewer above (235B-shaped NVFP4 layer, step us with 1 / 2 / 4 / 8
     // slices: T=64 264 / 259 / 257 / 258, T=256 318 / 313 / 311 / 322; 480B-shaped T=1000
     // 1,768 / 1,767 / 1,783 / 1,804).
-    if ((long)P.T * L.E > kTilePairs && L.E <= kTileE && P.k <= kTileK && P.ks_max > 0) {
+    if (tile_routes(L, P)) {
         const int tt = (P.T + 15) / 16, et = (L.E + 15) / 16;
         int ks = tt * et <= 256 ? 4 : (tt * et <= 512 ? 2 : 1);
         while (ks > 1 && (ks > P.ks_max || ks > L.H / 256)) ks /= 2;

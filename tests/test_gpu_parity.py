@@ -314,28 +314,36 @@ def test_exact_fallback_path(dev):
 
 def tiled(cfg, T, k=None):
     """Whether a step of this size takes the tiled routing."""
-    return T * cfg.n_experts > 6400 and cfg.n_experts <= 256 and (k or cfg.topk) <= 16 and cfg.hidden % 256 == 0
+    E, H = cfg.n_experts, cfg.hidden
+    if T * E <= 6400 or E > 256 or (k or cfg.topk) > 16 or H % 256:
+        return False
+    if cfg.act != "bf16" or cfg.router != "bf16":
+        return True
+    return T >= 50 if H >= 3072 else T * E >= 10000 and T >= (256 if E > 192 and H >= 2048 else 128)
 
 
-# (experts, top-k, hidden, activations, router, tokens): the tiled routing takes over above
-# 6,400 (token, expert) pairs, up to 256 experts and 16 choices; token and expert tiles of
-# 16 with remainders, 4 to 16 keys per lane, 1 to 4 slices of the inputs
-TILED = [(256, 16, 256, "bf16", "bf16", 26), (130, 3, 512, "bf16", "f32", 50), (160, 8, 1280, "f32", "bf16", 41),
-         (64, 1, 2048, "f32", "f32", 101), (65, 5, 768, "bf16", "bf16", 99), (16, 16, 512, "bf16", "bf16", 417),
-         (200, 16, 1024, "bf16", "bf16", 33), (257, 2, 256, "bf16", "bf16", 26), (160, 17, 256, "bf16", "bf16", 41),
-         (160, 8, 384, "bf16", "bf16", 41)]
+# (experts, top-k, hidden, activations, router, tokens on both sides of the switch to the
+# tiled routing, or past one of its limits: 256 experts, 16 choices, inputs in 256s); token
+# and expert tiles of 16 with remainders, 4 to 16 keys per lane, 1 to 4 slices of the inputs
+TILED = [(256, 16, 256, "bf16", "bf16", (127, 128)), (130, 3, 512, "bf16", "f32", (49, 50)),
+         (160, 8, 1280, "f32", "bf16", (40, 41)), (64, 1, 2048, "f32", "f32", (100, 101)),
+         (65, 5, 768, "bf16", "bf16", (153, 154)), (16, 16, 512, "bf16", "bf16", (624, 625)),
+         (200, 16, 1024, "bf16", "bf16", (127, 131)), (200, 4, 2048, "bf16", "bf16", (255, 256)),
+         (136, 4, 3072, "bf16", "bf16", (49, 50)), (257, 2, 256, "bf16", "bf16", (130,)),
+         (160, 17, 256, "bf16", "bf16", (130,)), (160, 8, 384, "bf16", "bf16", (130,))]
 
 
-@pytest.mark.parametrize("E,k,H,act,router,T", TILED, ids=lambda v: str(v))
-def test_tiled_routing(dev, E, k, H, act, router, T):
+@pytest.mark.parametrize("E,k,H,act,router,tokens", TILED, ids=lambda v: str(v))
+def test_tiled_routing(dev, E, k, H, act, router, tokens):
     """Bit-exact logits and selections on both sides of the switch to the tiled routing (and
     of its limits on experts, choices and inputs), with and without grouping; the screen
     asked for or not, which the tiled routing does not run."""
     cfg = LayerConfig(f"tiled-{E}-{k}-{H}", H, E, k, 256, act, router, "fp8", "normal:0.5", [])
     hl = W.host_layer(cfg, seed=517)
+    assert [tiled(cfg, t) for t in tokens] == ([False, True] if len(tokens) == 2 else [False])
     for screen in (-1, 1):
-        run = Run(cfg, hl, dev, max_tokens=T, screen_min_tokens=screen)
-        for t in {T, 6400 // E}:
+        run = Run(cfg, hl, dev, max_tokens=max(tokens), screen_min_tokens=screen)
+        for t in tokens:
             x = W.host_x(cfg, t, seed=517 + t)
             check_layer(run, x, label=f"{cfg.name} T={t} screen={screen}")
             st, _ = run.m.stats()
@@ -363,7 +371,8 @@ def test_tiled_routing_degenerate(dev, screen):
     hl.router_w[5, 1] = tiny24  # l = 1 + 2^-24: tie -> 1.0
     hl.router_w[6, 1] = tiny24  # l = 1 + 2^-24 + 2^-80: above the tie -> 1 + 2^-23
     hl.router_w[6, 2] = tiny80
-    T = 405
+    T = 641
+    assert tiled(cfg, T)
     x = np.zeros((T, cfg.hidden), np.uint16)
     x[:, 0] = x[:, 1] = x[:, 2] = one
     x[7] = 0
@@ -391,7 +400,8 @@ def test_tiled_routing_cancellation(dev, screen):
     pairs of random products that cancel and leave tiny logits of either sign."""
     cfg = LayerConfig("tiled-cancel", 512, 16, 4, 256, "bf16", "bf16", "fp8", None, [])
     hl = W.host_layer(cfg, seed=519)
-    T = 405
+    T = 641
+    assert tiled(cfg, T, 4)
     run = Run(cfg, hl, dev, max_tokens=T, screen_min_tokens=screen)
 
     def check(x, w, k, label):
@@ -401,7 +411,7 @@ def test_tiled_routing_cancellation(dev, screen):
         left = T * 16 - run.m.stats()[0].n_exact_logits  # uncertain, but below the top k
         say(f"[route] {label}: {left} of {T * 16} logits left uncertain")
         assert left > 0 if label.startswith("pairs") else left == 0
-        check_routing(run, _bf16(x[:401]), topk=k, label=f"tiled cancel {label}")
+        check_routing(run, _bf16(x[:633]), topk=k, label=f"tiled cancel {label}")
         return ids
 
     x, w = np.zeros((T, cfg.hidden)), np.zeros((16, cfg.hidden))
@@ -429,7 +439,7 @@ def test_tiled_routing_cancellation(dev, screen):
         check(x, w, k, f"pairs k={k}")
 
 
-@pytest.mark.parametrize("E,k,T", [(128, 8, 51), (160, 16, 41), (20, 4, 321)], ids=lambda v: str(v))
+@pytest.mark.parametrize("E,k,T", [(128, 8, 131), (160, 16, 129), (20, 4, 505)], ids=lambda v: str(v))
 @pytest.mark.parametrize("screen", [-1, 1], ids=["exact", "screened"])
 def test_tiled_routing_unordered_rows(dev, E, k, T, screen):
     """Tokens whose logits do not compare (NaN or infinite inputs) still get k different
@@ -439,7 +449,7 @@ def test_tiled_routing_unordered_rows(dev, E, k, T, screen):
     hl = W.host_layer(cfg, seed=520)
     run = Run(cfg, hl, dev, max_tokens=T, screen_min_tokens=screen)
     x = W.host_x(cfg, T, seed=520)
-    assert T * E > 6400
+    assert tiled(cfg, T)
     ids0, wts0, y0 = check_layer(run, x, label=f"{cfg.name} clean")
     bad = [0, 17, 18, T - 1]
     x[0] = 0x7FC0        # NaN
@@ -462,7 +472,8 @@ def test_tiled_routing_overflowing_logits(dev):
     infinite ones by index, none twice."""
     cfg = LayerConfig("tiled-overflow", 512, 16, 4, 256, "bf16", "bf16", "fp8", None, [])
     hl = W.host_layer(cfg, seed=521)
-    T = 405
+    T = 641
+    assert tiled(cfg, T)
     run = Run(cfg, hl, dev, max_tokens=T, screen_min_tokens=-1)
     x, w = np.zeros((T, cfg.hidden)), np.zeros((16, cfg.hidden))
     x[:, 0] = 2.0 ** 100
