@@ -1669,30 +1669,33 @@ __global__ void pack_scales_kernel(const uint8_t *__restrict__ src, uint8_t *__r
 //   NVFP4 row-major (whose 32-token kernels read 16 bytes of scales per row)  I 1536: 2
 //                  312 / 314, 4 357 / 334, 62 1,028 / 664; I 1024: 3 93 / 89; I 512: 8 76 /
 //                  81, 16 94 / 94
-// With one chunk per expert the two projections have E * (I / 128 + H / 256) items for 256
-// workgroups; where that is few, the 32-token kernels' many small workgroups fill the chip
-// and the weights saved count only from more tokens per expert.  Step us, 32-token / wide at
-// pairs per expert (uniform; Zipf-skewed 1.1; 2.5), under 448 items and under 1024:
-//   FP8 packed     352 items (H 4096, 16 experts, I 768): 32 79 / 83; 82 / 107; 70 / 112, 64
-//                  122 / 102; 116 / 133; 111 / 117, 96 159 / 125; 157 / 142; 141 / 134.  704
-//                  items (H 6144, 16 experts, I 2560): 16 at 0.78 of the speed, 24 at 0.87 on
-//                  average, 32 at 1.03, 48 at 1.28
-//   NVFP4          the same layers at 0.83 (32), 0.98 (48), 1.02 (56) packed and 0.92 (32),
-//                  1.04 (40) row-major; 704 to 768 items 0.90 (16), 0.99 (24), 1.06 (32)
-//                  packed, 0.85 to 0.94 (12), 0.94 to 1.06 (16) row-major
+// A chunk is I / 128 items of the gate/up projection and H / 256 of the down projection, for
+// 256 workgroups; where all items are few, the 32-token kernels' many small workgroups fill
+// the chip and the weights saved count only from more tokens.  So the wide kernels also need
+// pairs * min(I / 128, H / 256) of 7680 (NVFP4 6144 packed, 4608 row-major), and where one
+// chunk per expert gives under 1024 items 32 (30, 16) pairs per expert.  Speed against the
+// 32-token kernels, mean of uniform and two Zipf-skewed routings, at pairs per expert:
+//   FP8 packed     H 4096, 16 experts, I 768: 32 0.78, 64 1.01, 96 1.14; H 1024, 32 experts, I
+//                  512: 40 0.84, 64 1.06; 16 experts, I 256: 109 0.7; H 4096, 8 experts, I 4096: 32
+//                  0.92, 64 1.21; H 6144, 16 experts, I 2560: 16 0.79, 24 0.87, 32 1.03
+//   NVFP4          H 4096, 16 experts, I 768: 32 0.90, 48 0.98, 64 1.03 packed, 24 0.80, 40 1.04
+//                  row-major; H 1024, 32 experts, I 512: 40 0.95, 56 1.10 packed, 32 0.92, 48
+//                  1.07 row-major; H 6144, 16 experts, I 2560: 24 0.96, 32 1.07 packed, 12 0.89,
+//                  24 1.04 row-major
 int chunk_tokens(const Layer &L, int T, int k)
 {
-    const long pairs = (long)T * k, E = L.E, items = E * (L.I / 128 + L.H / 256);
-    const auto least = [&](int under448, int under1024) { return items < 448 ? under448 : items < 1024 ? under1024 : 0; };
+    const long pairs = (long)T * k, E = L.E;
+    const int t13 = L.I / 128, t2 = L.H / 256;
+    const long units = pairs * (t13 < t2 ? t13 : t2);
+    const bool few = E * (t13 + t2) < 1024, packed = L.wlayout != 0;
     if (L.wfmt == 0 && L.H % (32 * kWideW) == 0)
-        return pairs * L.I > (L.wlayout ? 20000 : 26000) * E && pairs >= least(64, 32) * E ? kWideChunk : kMfmaChunk;
-    if (L.wfmt == 2 && L.I % 128 == 0) {
-        const bool packed = L.wlayout != 0;
+        return pairs * L.I > (packed ? 20000 : 26000) * E && units >= 7680 && pairs >= (few ? 32 : 0) * E ? kWideChunk
+                                                                                                      : kMfmaChunk;
+    if (L.wfmt == 2 && L.I % 128 == 0)
         return pairs > (packed ? 13 : 3) * E && pairs * L.I > (packed ? 13000 : 7000) * E &&
-                       pairs >= (packed ? least(48, 30) : least(40, 16)) * E
+                       units >= (packed ? 6144 : 4608) && pairs >= (few ? (packed ? 30 : 16) : 0) * E
                    ? kWideChunk4
                    : kMfmaChunk;
-    }
     return kMfmaChunk;
 }
 

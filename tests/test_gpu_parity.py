@@ -683,34 +683,39 @@ def test_packed_mxfp4_skewed_chunks(dev, cfg, T):
 
 # The large-batch FP8 kernels (128-token chunks): K block counts of 6 and 5 (gate/up, down:
 # tails of two and one blocks), and of 4 and 3.
-WIDE_FP8 = [LayerConfig("wide-k6-5", 768, 8, 2, 640, "bf16", "bf16", "fp8", "zipf:1.1", []),
-            LayerConfig("wide-k4-3", 512, 8, 2, 384, "f32", "bf16", "fp8", "zipf:1.1", [])]
+WIDE_FP8 = [LayerConfig("wide-k6-5", 768, 16, 8, 640, "bf16", "bf16", "fp8", "zipf:1.1", []),
+            LayerConfig("wide-k4-3", 512, 16, 8, 384, "f32", "bf16", "fp8", "zipf:1.1", [])]
 
 
-def _items(cfg):
-    """Work items of the wide kernels with one chunk per expert."""
-    return cfg.n_experts * (cfg.inter // 128 + cfg.hidden // 256)
+def wide_from(cfg, packed):
+    """The fewest tokens of a step that takes the wide kernels, on a layer of few work items
+    (the rule of chunk_tokens)."""
+    E, t13, t2 = cfg.n_experts, cfg.inter // 128, cfg.hidden // 256
+    assert E * (t13 + t2) < 1024
+    if cfg.wfmt == "fp8":
+        pairs = max((20000 if packed else 26000) * E // cfg.inter + 1, -(-7680 // min(t13, t2)), 32 * E)
+    else:
+        pairs = max((13 if packed else 3) * E + 1, (13000 if packed else 7000) * E // cfg.inter + 1,
+                    -(-(6144 if packed else 4608) // min(t13, t2)), (30 if packed else 16) * E)
+    return -(-pairs // cfg.topk)
 
 
 @pytest.mark.parametrize("cfg", WIDE_FP8, ids=lambda c: c.name)
 @pytest.mark.parametrize("layout", [0, 1], ids=["rows", "packed"])
 def test_wide_chunks(dev, cfg, layout):
-    """FP8 layers on both sides of the switch to 128-token chunks (T*k*I above 20,000 per
-    expert packed, 26,000 row-major, and 64 pairs per expert on layers of few items).  The
-    Zipf-skewed batches give chunks of few tokens, of every number of token-tile pairs (2, 4,
-    6, 8 tiles) and, at the largest, several chunks of one expert."""
+    """FP8 layers on both sides of the switch to 128-token chunks.  The Zipf-skewed batches
+    give chunks of few tokens, of every number of token-tile pairs (2, 4, 6, 8 tiles) and
+    several chunks of one expert."""
     hl = W.host_layer(cfg, seed=611)
-    per = 26000 if layout == 0 else 20000
-    edge = max(per * cfg.n_experts // (cfg.topk * cfg.inter),
-               64 * cfg.n_experts // cfg.topk - 1)
-    assert _items(cfg) < 448
+    first = wide_from(cfg, layout == 1)
+    assert first < 640
     run = Run(cfg, hl, dev, max_tokens=700, weight_layout=layout)
     sizes = set()
-    for T in (edge, edge + 1, 340, 700):
+    for T in (first - 1, first, 640, 700):
         check_layer(run, W.host_x(cfg, T, seed=611 + T), label=f"{cfg.name} T={T}")
         _, counts = run.m.stats()
         say(f"[wide] {cfg.name} T={T}: tokens per expert {sorted(counts, reverse=True)}")
-        if T > edge:
+        if T >= first:
             for c in counts:
                 sizes |= {128} if c >= 128 else set()
                 sizes |= {c % 128} - {0}
@@ -721,29 +726,25 @@ def test_wide_chunks(dev, cfg, layout):
 
 # The large-batch NVFP4 kernels (64-token chunks): K block counts of 5 and 3, 2 and 1, and 8
 # and 4 (grouped packed scales in both projections).
-WIDE_NV = [LayerConfig("nv-wide-k5-3", 1280, 8, 2, 768, "bf16", "bf16", "nvfp4", "zipf:1.1", []),
-           LayerConfig("nv-wide-k2-1", 512, 8, 2, 256, "bf16", "bf16", "nvfp4", "zipf:1.1", []),
-           LayerConfig("nv-wide-k8-4", 2048, 8, 2, 1024, "bf16", "bf16", "nvfp4", "zipf:1.1", [])]
+WIDE_NV = [LayerConfig("nv-wide-k5-3", 1280, 16, 8, 768, "bf16", "bf16", "nvfp4", "zipf:1.1", []),
+           LayerConfig("nv-wide-k2-1", 512, 16, 8, 256, "bf16", "bf16", "nvfp4", "zipf:1.1", []),
+           LayerConfig("nv-wide-k8-4", 2048, 16, 8, 1024, "bf16", "bf16", "nvfp4", "zipf:1.1", [])]
 
 
 @pytest.mark.parametrize("cfg", WIDE_NV, ids=lambda c: c.name)
 @pytest.mark.parametrize("layout", [0, 1], ids=["rows", "packed"])
 def test_nvfp4_wide_chunks(dev, cfg, layout):
-    """NVFP4 layers on both sides of the switch to 64-token chunks (more than 13 pairs and
-    T*k*I above 13,000 per expert packed, 3 and 7,000 row-major; on these layers of few items
-    from 48 and 40 pairs); the Zipf-skewed batches give chunks of both token-tile counts and
-    several chunks of one expert."""
+    """NVFP4 layers on both sides of the switch to 64-token chunks; the Zipf-skewed batches
+    give chunks of both token-tile counts and several chunks of one expert."""
     hl = W.host_layer(cfg, seed=621)
-    assert _items(cfg) < 448
-    per = max(13, 13000 // cfg.inter, 47) if layout else max(3, 7000 // cfg.inter, 39)
-    edge = per * cfg.n_experts // cfg.topk
-    run = Run(cfg, hl, dev, max_tokens=300, weight_layout=layout)
+    first = wide_from(cfg, layout == 1)
+    run = Run(cfg, hl, dev, max_tokens=first + 80, weight_layout=layout)
     sizes = set()
-    for T in (edge, edge + cfg.n_experts, 300):
+    for T in (first - 1, first, first + 80):
         check_layer(run, W.host_x(cfg, T, seed=621 + T), label=f"{cfg.name} T={T}")
         _, counts = run.m.stats()
         say(f"[wide] {cfg.name} T={T}: tokens per expert {sorted(counts, reverse=True)}")
-        if T > edge:
+        if T >= first:
             sizes |= {c % 64 for c in counts} | {64 * (c >= 64) for c in counts}
     assert max(counts) > 128
     assert any(1 <= n <= 32 for n in sizes) and any(33 <= n <= 64 for n in sizes)
