@@ -1524,13 +1524,17 @@ hipError_t launch_route(const Layer &L, const RouteParams &P, hipStream_t st)
     if (A.id_cache) lds += 2 * pairs;
     if (!P.do_group) lds = 0;
     // Tiled routing, also where the screen was asked for; it needs H a multiple of 256 (ks_max
-    // > 0: the workspace holds no partial sums otherwise).  Four slices of the inputs while the tiles are
-    // at most one per CU, fewer above (235B-shaped NVFP4 layer, step us with 1 / 2 / 4 / 8
-    // slices: T=64 264 / 259 / 257 / 258, T=256 318 / 313 / 311 / 322; 480B-shaped T=1000
-    // 1,768 / 1,767 / 1,783 / 1,804).
+    // > 0: the workspace holds no partial sums otherwise).  As many slices of the inputs as
+    // give one round of resident workgroups (two per CU), two up to 352 tiles of long inputs,
+    // whose slices outweigh a second round.  Step us with 1 / 2 / 4 / 8 slices: 235B-shaped
+    // NVFP4 layer, T=64 264 / 259 / 257 / 258, T=256 (128 tiles) 318 / 313 / 311 / 322;
+    // 480B-shaped T=1000 (630) 1,768 / 1,767 / 1,783 / 1,804.  Against four slices up to 256
+    // tiles and two up to 512: 160 experts of 2,048 inputs T=256 (160 tiles) -6.6, T=336
+    // (210) -9.5; 256 of 2,048 T=256 (256) -12; 128 of 2,048 T=384 (192) -7.7; with one slice
+    // from 257: 160 of 6,144 T=432 (270) +5.1, 256 of 6,144 T=336 (336) +5.9, T=432 (432) -3.4.
     if (tile_routes(L, P)) {
         const int tt = (P.T + 15) / 16, et = (L.E + 15) / 16;
-        int ks = tt * et <= 256 ? 4 : (tt * et <= 512 ? 2 : 1);
+        int ks = tt * et <= 128 ? 4 : (tt * et <= (L.H >= 4096 ? 352 : 256) ? 2 : 1);
         while (ks > 1 && (ks > P.ks_max || ks > L.H / 256)) ks /= 2;
         A.KS = ks;
         const size_t lf = (size_t)16 * L.E * sizeof(float), bytes = lds > lf ? lds : lf;
