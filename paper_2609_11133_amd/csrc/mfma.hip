@@ -1722,20 +1722,26 @@ hipError_t launch_w2_mfma(const Layer &L, const void *expert_w, const void *scal
 }
 
 // The owner kernel saves a launch and the expert outputs' round trip, but a CU streams no
-// more than about 24 GB/s through it, so it needs an even share of the rows on every CU, or
-// so few pairs that launches and latency are the cost.  Step us, other kernels / this one:
-// one token, 235B-shaped FP8 44.1 / 42.1, MXFP4 42.1 / 40.3, H 2048 28.3 / 26.2, H 1024 23.2 /
-// 21.8, but 384 workgroups on 256 CUs (H 6144) 39.3 / 40.4; 24 pairs, H 2048 45.5 / 46.2, H
-// 1024 28.2 / 29.6.  With 256 workgroups (H 4096) and FP8 weights whose rows are too short for
-// the staged kernel it stays ahead up to 8 tokens, one pass per expert: 235B-shaped T=4 106.0 /
-// 104.7, T=8 163 / 159, Zipf-skewed T=8 86.9 / 86.0.  Above, an expert's further passes stream
-// its weights again: uniform T=32 343 / 339, but skewed T=12 98.3 / 101, T=16 103 / 108, T=64 209
-// / 234.  MXFP4 T=4 73.0 / 76.2.
+// more than about 24 GB/s through it, so it needs an even share of the rows on most CUs (192
+// to 255 workgroups, or a multiple of 256), or so few pairs that launches and latency are the
+// cost.  Step us, other kernels / this one: one token, 235B-shaped FP8 44.1 / 42.1, MXFP4 42.1 /
+// 40.3, H 2048 28.3 / 26.2, H 1024 23.2 / 21.8, but 384 workgroups on 256 CUs (H 6144) 39.3 /
+// 40.4; 24 pairs, H 2048 45.5 / 46.2, H 1024 28.2 / 29.6.
+// FP8 weights, up to 8 tokens, one pass per expert: 235B-shaped T=4 106.0 / 104.7, T=8 163 / 159,
+// Zipf-skewed T=8 86.9 / 86.0; 192 workgroups (H 3072, I 1280) T=4 51.5 / 48.8, 224 (H 3584, I
+// 1024) T=8 93.9 / 90.5, 240 (H 3840, I 1536) T=8 150.0 / 147.1.  Row-major weights only on an
+// even share: 192 workgroups T=6 63.2 / 67.0, 240 T=8 skewed 114.4 / 114.9, but 256 (I 2048) 149.5 /
+// 143.7; rows above 2048 not: I 2560 on 208 workgroups packed T=6 skewed 60.2 / 62.6, row-major T=8
+// 156 / 161, on 256 row-major skewed 113.8 / 119.0.  Above 8 tokens an expert's further passes
+// stream its weights again: uniform T=32 343 / 339, but skewed T=12 98.3 / 101, T=16 103 / 108,
+// T=64 209 / 234.  MXFP4 T=4 73.0 / 76.2.
 // NVFP4 weights, whose conversion a second pass of an expert repeats: up to 12 tokens, where
-// skewed routing still breaks even, if most CUs have a workgroup: 235B-shaped T=8 111.8 / 106.3
-// and Zipf-skewed 64.5 / 64.0, T=12 143.8 / 139.6 and 71.2 / 71.2, T=24 202.0 / 197.0 but
-// skewed 97.5 / 99.0 (row-major 120 / 130); 240 workgroups T=8 63.6 / 59.8, 208 T=3 32.2 / 29.3;
-// 64 workgroups (H 1024) T=8 63.6 / 78.7, 384 (H 6144) T=8 246 / 253.
+// skewed routing is about even: 235B-shaped T=8 111.8 / 106.3 and Zipf-skewed 64.5 / 64.0, T=12
+// 143.8 / 139.6 and 71.2 / 71.2, T=24 202.0 / 197.0 but skewed 97.5 / 99.0; row-major T=10 169.8 /
+// 161.0 and skewed 82.2 / 84.0, T=12 204.8 / 193.2 and 94.2 / 96.3, T=24 skewed 120 / 130 (with all
+// tokens on the same few experts it loses from T=6 row-major, 46.4 / 48.9, and T=10 packed, 48.4 /
+// 50.6); 240 workgroups T=8 63.6 / 59.8, 208 T=3 32.2 / 29.3; 64 (H 1024) T=8 63.6 / 78.7, 384 (H
+// 6144) T=8 246 / 253.
 bool w2_combines(const Layer &L, int T, int k)
 {
     const long pairs = (long)T * k, active = pairs < L.E ? pairs : L.E;
@@ -1744,8 +1750,9 @@ bool w2_combines(const Layer &L, int T, int k)
         return false;
     const int blocks = L.H / 16;
     if (pairs <= 8 && blocks <= 256) return true;
-    if (L.wfmt == 2) return T <= 12 && (blocks % 256 == 0 || (blocks >= 192 && blocks < 256));
-    return L.wfmt == 0 && T <= 8 && blocks % 256 == 0 && L.I < 2048;
+    const bool even = blocks % 256 == 0, most = blocks >= 192 && blocks < 256;
+    if (L.wfmt == 2) return T <= 12 && (even || most);
+    return L.wfmt == 0 && T <= 8 && L.I <= 2048 && (even || (most && L.wlayout));
 }
 
 template <int FMT, bool PK, bool OUTF32>

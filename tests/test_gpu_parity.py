@@ -751,15 +751,19 @@ def test_nvfp4_wide_chunks(dev, cfg, layout):
 
 
 # (layer, top-k, tokens): the down projection that combines, taken up to 8 pairs, and for FP8
-# layers of H = 4096 and I < 2048 up to 8 tokens; K block counts from 1 to 12 around its ring
-# of four, passes of up to eight tokens, and the token and pair counts next to its limits; NVFP4 layers up to 12 tokens (or 8 pairs) in passes
-# of four and eight, with each scale layout (K block counts 1, 3, 4 and 5)
+# layers of I up to 2048 up to 8 tokens where its row blocks fill the CUs evenly (H 4096) or,
+# packed, at least three quarters of them; K block counts from 1 to 16 around its ring of
+# four, passes of up to eight tokens, and the token and pair counts next to its limits; NVFP4
+# layers up to 12 tokens (or 8 pairs) in passes of four and eight, with each scale layout (K
+# block counts 1, 3, 4 and 5)
 OWN = [(LayerConfig("own-k1", 256, 8, 2, 128, "f32", "f32", "fp8", None, []), (1, 3, 4, 5)),
        (LayerConfig("own-k5", 640, 16, 4, 640, "bf16", "bf16", "fp8", "normal:0.5", []), (1, 2, 3)),
        (LayerConfig("own-mx-k6", 1024, 8, 1, 768, "bf16", "bf16", "mxfp4", "zipf:1.1", []), (1, 7, 8, 9)),
        (LayerConfig("own-mx-k4", 512, 4, 4, 512, "f32", "bf16", "mxfp4", "zipf:1.1", []), (1, 2)),
        (LayerConfig("own-h4096", 4096, 16, 4, 384, "bf16", "bf16", "fp8", "zipf:1.1", []), (3, 7, 8, 9)),
        (LayerConfig("own-h4096-k3", 4096, 24, 3, 1152, "f32", "bf16", "fp8", None, []), (8,)),
+       (LayerConfig("own-h3072", 3072, 12, 4, 2048, "bf16", "bf16", "fp8", "zipf:1.1", []), (3, 8, 9)),
+       (LayerConfig("own-h3968", 3968, 12, 2, 256, "f32", "f32", "fp8", None, []), (5, 8)),
        (LayerConfig("own-nv-k1", 256, 8, 2, 256, "bf16", "bf16", "nvfp4", None, []), (1, 3, 4, 5)),
        (LayerConfig("own-nv-k4", 3072, 16, 4, 1024, "bf16", "f32", "nvfp4", "zipf:1.1", []), (1, 2, 4, 5, 12, 13)),
        (LayerConfig("own-nv-h4096", 4096, 64, 3, 768, "bf16", "bf16", "nvfp4", "normal:0.5", []), (4, 10, 11, 12)),
