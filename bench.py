@@ -48,7 +48,7 @@ METRIC = "MoE decode-layer tokens/s and achieved HBM GB/s (% of peak) vs batch s
 CSRC = os.path.join(ROOT, "paper_2609_11133_amd", "csrc")
 # sources the gate/up MFMA kernel is compiled from: a counter profile is valid only
 # for the kernel it was taken on
-W13_SOURCES = ["mfma.hip", "fp8split.h", "moe_internal.h"]
+W13_SOURCES = ["mfma.hip", "fp8split.h", "moe_internal.h", "own.h", "wave.h"]
 
 
 def w13_source_hash() -> str:

@@ -888,8 +888,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 8 ?
 // so only the first activations of an item are waited for.
 //
 // Measured, us (gate/up and down by the stage events, 32-token chunks -> these): the
-// 480B-shaped layer with biased routing at T=1000 1,845 -> 1,038 and 1,013 -> 564 (5.8 GB
-// and 2.9 GB of weight streams: 5.6 and 5.1 TB/s); uniform routing T=600 1,179 -> 882 and
+// 480B-shaped layer with biased routing at T=1000 1,845 -> 1,038 and 1,013 -> 564 (6.4 GB
+// and 3.1 GB fetched by the counters, with the writes 6.2 and 5.9 TB/s, where a read-only
+// stream reaches 6.8); uniform routing T=600 1,179 -> 882 and
 // 672 -> 498.  At T=600 the same kernel without its activation staging takes 810 and 454,
 // and without MFMAs 867 and 491: what is left is the staging and, in the down projection,
 // its shorter items.  Four-wave workgroups (two per CU) lost, 934 -> 1,287 at T=600: they

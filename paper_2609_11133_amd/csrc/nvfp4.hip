@@ -489,6 +489,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(T16 ? 3 
 // 235B-shaped layer at T=256 with Zipf-skewed routing 159 -> 143 and 110 -> 94; step at
 // T=500 464 -> 379, at T=1000 820 -> 604 (gate/up 274, down 180: 1.5 weight streams per
 // expert at 4.9 TB/s); row-major weights at T=1000 1,028 -> 664.
+//
+// A block's products go into one accumulator per tile and token tile, where the 32-token
+// kernels add two halves: h may differ from theirs in its last bf16 bit (2e-4 of the output
+// on the Zipf-skewed T=256 step; both are 2.4e-3 from the 64-bit result).
 
 constexpr int kWW = 8;           // waves per workgroup
 constexpr int kWGrid = 256;      // persistent workgroups: one per CU
