@@ -492,7 +492,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(T16 ? 3 
 //
 // A block's products go into one accumulator per tile and token tile, where the 32-token
 // kernels add two halves: h may differ from theirs in its last bf16 bit (2e-4 of the output
-// on the Zipf-skewed T=256 step; both are 2.4e-3 from the 64-bit result).
+// on the Zipf-skewed T=256 step; both are 2.3e-3 from the 64-bit result).
 
 constexpr int kWW = 8;           // waves per workgroup
 constexpr int kWGrid = 256;      // persistent workgroups: one per CU

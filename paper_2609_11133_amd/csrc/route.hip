@@ -1114,7 +1114,7 @@ __global__ __launch_bounds__(256) void route_cand_kernel(RouteArgs A)
 
 // ------------------------------------------------------------------ tiled routing
 //
-// From a few tokens on, the logits come from fp64 matrix-core sums: workgroup (ks, y, z)
+// Where tile_routes says so, the logits come from fp64 matrix-core sums: workgroup (ks, y, z)
 // forms the 16 x 16 products of experts 16y.. and tokens 16z.. over slice ks of the inputs
 // (v_mfma_f64_16x16x4: products of bf16 or fp32 operands are exact in fp64), so each
 // operand is converted once for sixteen products; converting and adding every product on
@@ -1126,10 +1126,11 @@ __global__ __launch_bounds__(256) void route_cand_kernel(RouteArgs A)
 // top-k softmax of the sixteen tokens, a token per 16-lane row, four to a wave.  The last
 // token tile groups the pairs.
 //
-// Measured by device timestamps, us from the workgroup's start (480B-shaped T=64; 235B-shaped
-// T=256): sums 6.8, 7.2; handed over 9.2, 9.7; certified 13.4, 12.3; top k 15.7, 14.2; written
-// 16.8, 15.5; grouped 21, 25.  Step us, before / now: 235B-shaped NVFP4 T=127 282 / 274;
-// screened, T=256 320 / 313, 480B-shaped T=1000 1,854 / 1,768 (routing 160 / 62).
+// What bounds it is that chain of dependent phases.  Device timestamps, us from the
+// workgroup's start (480B-shaped T=64; 235B-shaped T=256): sums 6.8, 7.2; handed over 9.2,
+// 9.7; certified 13.4, 12.3; top k 15.7, 14.2; written 16.8, 15.5; grouped 21, 25.  The whole
+// kernel by rocprofv3, us: 23 and 25; 480B-shaped T=1000 92.  Step us, before / now:
+// 235B-shaped NVFP4 T=127 282 / 274; 480B-shaped T=1000 1,854 / 1,753; T=64 even (908 / 906).
 
 constexpr int kTileE = 256;  // experts at most (16 keys per lane)
 constexpr int kTileK = 16;   // choices at most (one per lane of a row)
